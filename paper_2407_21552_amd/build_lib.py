@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpdm.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = [os.path.join(CSRC, "pdm_kernels.hip"), os.path.join(CSRC, "pdm_api.cpp")]
+SOURCES = [os.path.join(CSRC, f) for f in ("pdm_kernels.hip", "pdm_sweep.hip", "pdm_api.cpp")]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # no packed fp32 instructions in device code

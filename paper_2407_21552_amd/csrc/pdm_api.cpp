@@ -126,6 +126,16 @@ pdm_status plain_args(const pdm_volume* v, const void* d_volume, const float* h_
     return PDM_OK;
 }
 
+// The second phase of the builds: x distances written by this library's own x
+// passes, which the sweeps may take (pdm_distance_yz takes any bytes).
+pdm_status complete(const pdm_volume* v, uint8_t* d_maps, int32_t count, hipStream_t stream) {
+    pdm_grid g;
+    const pdm_status st = check_volume(v, &g);
+    if (st != PDM_OK) return st;
+    return from_hip(pdm::sweep_fits(count, g.bx, g.by, g.bz)
+                        ? pdm::launch_sweep(d_maps, count, g.bx, g.by, g.bz, stream)
+                        : pdm::launch_distance_yz(d_maps, count, g.bx, g.by, g.bz, stream));
+}
 
 }  // namespace
 
@@ -211,7 +221,7 @@ pdm_status pdm_build_partitions(const pdm_volume* v, const void* d_bmin, const v
                                 hipStream_t stream) {
     pdm_status st = pdm_pom_distance_x(v, d_bmin, d_bmax, h_bounds, n, d_pdms, stream);
     if (st != PDM_OK) return st;
-    return pdm_distance_yz(v, d_pdms, n, stream);
+    return complete(v, d_pdms, n, stream);
 }
 
 pdm_status pdm_tf_update(const pdm_volume* v, const uint8_t* d_pdms, const int32_t* h_bounds,
@@ -505,6 +515,8 @@ pdm_status batch_prepare(const pdm_batch_volume* h_vols, int32_t count, const pd
                 order[b - 1] = t;
             }
     for (int32_t k = 0; k < count; ++k) vols[k] = tmp[order[k]];
+    // grouped launches: the y and z phases by sweeps where those are faster
+    if (c.single_launch == 0 && pdm::batch_sweep_fits(vols, count)) pdm::batch_sweep_items(vols, count);
     totals[0] = totals[1] = totals[2] = 0;
     for (int ph = 0; ph < 3; ++ph)
         for (int32_t k = 0; k < count; ++k) {
@@ -653,7 +665,7 @@ pdm_status pdm_build_partitions_exact(const pdm_volume* v, const void* d_volume,
                                       hipStream_t stream) {
     pdm_status st = pdm_pom_exact_distance_x(v, d_volume, h_bounds, n, d_pdms, stream);
     if (st != PDM_OK) return st;
-    return pdm_distance_yz(v, d_pdms, n, stream);
+    return complete(v, d_pdms, n, stream);
 }
 
 pdm_status pdm_plain_exact_distance_x(const pdm_volume* v, const void* d_volume,

@@ -90,7 +90,9 @@ struct BatchVol {
     int32_t rows;        // brick rows per first-phase item
     int32_t row_groups;  // first-phase items per z slice: ceil(By / rows)
     int32_t row_lanes;   // lanes per brick row in the first phase (power of two)
-    int32_t pad1[6];
+    int32_t sweep_items[2];  // sweep work-groups, planes of many rows and of few (0: line scans)
+    int32_t sweep_first[2];  // first of them within its launch
+    int32_t pad1[2];
     int32_t bounds[257];
 };
 
@@ -149,6 +151,13 @@ struct PomExactArgs {
     int store_vec;
 };
 
+// Raster sweeps over the maps of one grid (pdm_sweep.hip).
+struct SweepArgs {
+    int64_t G;
+    int count, Bx, By, Bz;
+    int W;  // lanes per row
+};
+
 hipError_t launch_bricks(const BrickArgs& a, hipStream_t s);
 hipError_t launch_pom_x(const PomArgs& a, const Bounds& b, hipStream_t s);
 hipError_t launch_plain_x(const PlainArgs& a, const AlphaBits& bits, hipStream_t s);
@@ -171,6 +180,16 @@ hipError_t launch_batch_build(const BatchVol* h_vols, int count, BatchVol* d_vol
 hipError_t batch_scratch(int dev, uint8_t** ptr, size_t* bytes);
 // *dst = *src (one word, device memory), on the stream.
 hipError_t launch_copy_word(const uint32_t* src, uint32_t* dst, hipStream_t s);
+// Completes `count` grids of x distances (rows of distances along x, not any
+// bytes) by raster sweeps; the caller asks sweep_fits first.
+bool sweep_fits(int count, int Bx, int By, int Bz);
+hipError_t launch_sweep(uint8_t* maps, int count, int Bx, int By, int Bz, hipStream_t s);
+// The same for the y and z phases of a batched build: whether the batch takes
+// the sweeps, the volumes' work-groups (items of the y and z phases zeroed),
+// and the launches, after the rows phase.
+bool batch_sweep_fits(const BatchVol* vols, int count);
+void batch_sweep_items(BatchVol* vols, int count);
+hipError_t launch_batch_sweep(const BatchVol* h_vols, int count, const BatchVol* d_vols, hipStream_t s);
 hipError_t launch_distance_yz(uint8_t* maps, int count, int Bx, int By, int Bz, hipStream_t s);
 // out = element-wise min of the listed maps of G bytes (255 for none); any
 // size and pointer alignment.
