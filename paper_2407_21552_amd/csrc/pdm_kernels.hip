@@ -105,40 +105,69 @@ __device__ __forceinline__ uint2 load8(VP p) {
     return w;
 }
 
-// The quad's 16 voxel rows, x in [x0, x0 + 16) inside the row: row i is
-// (z0 + i/4, y0 + i%4).  With CLAMP (a brick layer cut by the volume's end
-// in z or y) rows past the volume repeat its last row, which never changes a
-// brick's min or max; every load is issued before the first use.
-template <typename T, bool CLAMP, typename VP>
-__device__ __forceinline__ QuadMinMax<T> quad_whole_rows(VP __restrict__ vol, int nx, int ny,
-                                                         int z0, int y0, int zn, int yn, int x0) {
-    QuadMinMax<T> r;
-    const int64_t base = ((int64_t)z0 * ny + y0) * nx + x0;
-    auto off = [&](int i) -> int64_t {
-        const int zz = CLAMP ? min(i >> 2, zn - 1) : (i >> 2);
-        const int yy = CLAMP ? min(i & 3, yn - 1) : (i & 3);
-        return base + ((int64_t)zz * ny + yy) * nx;
-    };
-    if constexpr (sizeof(T) == 1) {
-        u32x4 w[16];
+// Moves the packed voxels of w down by n voxels (of B bytes), n < 16, the top
+// filled with `fill`: w[0] then starts with voxel n.
+template <int B, int N>
+__device__ __forceinline__ void shift_voxels(uint32_t (&w)[N], int n, uint32_t fill) {
+    const int bytes = n * B, words = bytes >> 2;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) w[i] = load16_nt(vol + off(i));
-        // even/odd byte lanes held as packed u16 pairs, one pair per brick
-        uint32_t mnE[4], mnO[4], mxE[4], mxO[4];
+    for (int step = N / 2; step >= 1; step /= 2)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) { mnE[k] = mnO[k] = 0xFFFFFFFFu; mxE[k] = mxO[k] = 0u; }
+        for (int i = 0; i < N; ++i)
+            if (words & step) w[i] = i + step < N ? w[i + step] : fill;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const uint32_t ws[4] = {w[i].x, w[i].y, w[i].z, w[i].w};
+    for (int i = 0; i < N; ++i)
+        w[i] = __builtin_amdgcn_alignbyte(i + 1 < N ? w[i + 1] : fill, w[i], (uint32_t)bytes & 3u);
+}
+
+// Minimum and maximum over the quad's 16 voxel rows, voxel column by voxel
+// column, then brick by brick.
+template <typename T>
+struct QuadColumns;
+
+template <>
+struct QuadColumns<uint8_t> {
+    // even/odd byte lanes held as packed u16 pairs, one pair per brick
+    uint32_t mnE[4], mnO[4], mxE[4], mxO[4];
+
+    __device__ __forceinline__ QuadColumns() {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint32_t e = even_bytes(ws[k]), o = odd_bytes(ws[k]);
-                mnE[k] = pk_min16(mnE[k], e);
-                mnO[k] = pk_min16(mnO[k], o);
-                mxE[k] = pk_max16(mxE[k], e);
-                mxO[k] = pk_max16(mxO[k], o);
-            }
+        for (int k = 0; k < 4; ++k) {
+            mnE[k] = mnO[k] = 0xFFFFFFFFu;
+            mxE[k] = mxO[k] = 0u;
         }
+    }
+    __device__ __forceinline__ void add(const u32x4 w) {
+        const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t e = even_bytes(ws[k]), o = odd_bytes(ws[k]);
+            mnE[k] = pk_min16(mnE[k], e);
+            mnO[k] = pk_min16(mnO[k], o);
+            mxE[k] = pk_max16(mxE[k], e);
+            mxO[k] = pk_max16(mxO[k], o);
+        }
+    }
+    // the columns n voxels further on
+    __device__ __forceinline__ void shift(int n) {
+        uint32_t a[4], b[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            a[k] = even_bytes(mnE[k]) | (even_bytes(mnO[k]) << 8);
+            b[k] = mxE[k] | (mxO[k] << 8);
+        }
+        shift_voxels<1>(a, n, 0xFFFFFFFFu);
+        shift_voxels<1>(b, n, 0u);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            mnE[k] = even_bytes(a[k]);
+            mnO[k] = odd_bytes(a[k]);
+            mxE[k] = even_bytes(b[k]);
+            mxO[k] = odd_bytes(b[k]);
+        }
+    }
+    __device__ __forceinline__ QuadMinMax<uint8_t> bricks() const {
+        QuadMinMax<uint8_t> r;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const uint32_t a = pk_min16(mnE[k], mnO[k]);
@@ -146,11 +175,73 @@ __device__ __forceinline__ QuadMinMax<T> quad_whole_rows(VP __restrict__ vol, in
             r.mn[k] = umin(lo16(a), hi16(a));
             r.mx[k] = umax(lo16(b), hi16(b));
         }
+        return r;
+    }
+};
+
+template <>
+struct QuadColumns<uint16_t> {
+    uint32_t mn[8], mx[8];  // two voxels per word, two words per brick
+
+    __device__ __forceinline__ QuadColumns() {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            mn[k] = 0xFFFFFFFFu;
+            mx[k] = 0u;
+        }
+    }
+    __device__ __forceinline__ void add(const u32x4 a, const u32x4 b) {
+        const uint32_t ws[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            mn[k] = pk_min16(mn[k], ws[k]);
+            mx[k] = pk_max16(mx[k], ws[k]);
+        }
+    }
+    __device__ __forceinline__ void shift(int n) {
+        shift_voxels<2>(mn, n, 0xFFFFFFFFu);
+        shift_voxels<2>(mx, n, 0u);
+    }
+    __device__ __forceinline__ QuadMinMax<uint16_t> bricks() const {
+        QuadMinMax<uint16_t> r;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t a = pk_min16(mn[2 * k], mn[2 * k + 1]);
+            const uint32_t b = pk_max16(mx[2 * k], mx[2 * k + 1]);
+            r.mn[k] = umin(lo16(a), hi16(a));
+            r.mx[k] = umax(lo16(b), hi16(b));
+        }
+        return r;
+    }
+};
+
+// The quad's 16 voxel rows (row i is (z0 + i/4, y0 + i%4)) of a volume at least
+// 16 voxels wide.  With CLAMP (a brick layer cut by the volume's end in z or
+// y) rows past the volume repeat its last row, which never changes a brick's
+// min or max; every load is issued before the first use.  A quad that runs
+// past the row end loads the row's last 16 voxels and moves the columns'
+// results up to its own, once (voxels past the end take no part): the same
+// loads for every lane of the wave, where a path of its own for that lane
+// cost four more rounds of loads in every row.
+template <typename T, bool CLAMP, bool EDGE, typename VP>
+__device__ __forceinline__ QuadMinMax<T> quad_whole_rows(VP __restrict__ vol, int nx, int ny,
+                                                         int z0, int y0, int zn, int yn, int x0) {
+    const int xp = EDGE ? min(x0, nx - 16) : x0;
+    const int64_t base = ((int64_t)z0 * ny + y0) * nx + xp;
+    auto off = [&](int i) -> int64_t {
+        const int zz = CLAMP ? min(i >> 2, zn - 1) : (i >> 2);
+        const int yy = CLAMP ? min(i & 3, yn - 1) : (i & 3);
+        return base + ((int64_t)zz * ny + yy) * nx;
+    };
+    QuadColumns<T> c;
+    if constexpr (sizeof(T) == 1) {
+        u32x4 w[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) w[i] = load16_nt(vol + off(i));
+#pragma unroll
+        for (int i = 0; i < 16; ++i) c.add(w[i]);
     } else {
         // u16: 32 bytes per row; two rounds of 8 rows (16 loads each)
-        uint32_t mn[4], mx[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) { mn[k] = 0xFFFFFFFFu; mx[k] = 0u; }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             u32x4 w[16];
@@ -161,26 +252,16 @@ __device__ __forceinline__ QuadMinMax<T> quad_whole_rows(VP __restrict__ vol, in
                 w[2 * i + 1] = load16_nt(vol + o + 8);
             }
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const uint32_t ws[8] = {w[2 * i].x, w[2 * i].y, w[2 * i].z, w[2 * i].w,
-                                        w[2 * i + 1].x, w[2 * i + 1].y, w[2 * i + 1].z, w[2 * i + 1].w};
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    mn[k] = pk_min16(mn[k], pk_min16(ws[2 * k], ws[2 * k + 1]));
-                    mx[k] = pk_max16(mx[k], pk_max16(ws[2 * k], ws[2 * k + 1]));
-                }
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            r.mn[k] = umin(lo16(mn[k]), hi16(mn[k]));
-            r.mx[k] = umax(lo16(mx[k]), hi16(mx[k]));
+            for (int i = 0; i < 8; ++i) c.add(w[2 * i], w[2 * i + 1]);
         }
     }
-    return r;
+    if constexpr (EDGE) {
+        if (xp != x0) c.shift(x0 - xp);
+    }
+    return c.bricks();
 }
 
-// The quad's rows when its 16 voxels run past the row end (nx >= 4): brick
+// The quad's rows in a volume of 4 to 15 voxels in x: brick
 // k's 4 voxels are loaded at min(x0 + 4k, nx - 4), so every load stays in
 // the row; when that start is pulled back, its first voxels belong to the
 // brick before and are masked out (to the maximum value for the min, to 0
@@ -239,93 +320,62 @@ __device__ __forceinline__ QuadMinMax<T> quad_ragged_rows(VP __restrict__ vol, i
 }
 
 // The quad's rows one at a time (a brick layer cut in z or y): few registers.
-template <typename T, typename VP>
+template <typename T, bool EDGE, typename VP>
 __device__ __forceinline__ QuadMinMax<T> quad_rows_looped(VP __restrict__ vol, int nx, int ny,
                                                           int z0, int y0, int zn, int yn, int x0) {
-    QuadMinMax<T> r;
-    if constexpr (sizeof(T) == 1) {
-        // even/odd byte lanes held as packed u16 pairs, one pair per brick
-        uint32_t mnE[4], mnO[4], mxE[4], mxO[4];
+    const int xp = EDGE ? min(x0, nx - 16) : x0;
+    QuadColumns<T> c;
+    for (int zz = 0; zz < zn; ++zz) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) { mnE[k] = mnO[k] = 0xFFFFFFFFu; mxE[k] = mxO[k] = 0u; }
-        for (int zz = 0; zz < zn; ++zz) {
-#pragma unroll
-            for (int yy = 0; yy < 4; ++yy) {
-                if (yy < yn) {
-                    const int64_t off = ((int64_t)(z0 + zz) * ny + (y0 + yy)) * nx + x0;
-                    const uint4 w = load16(vol + off);
-                    const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const uint32_t e = even_bytes(ws[k]), o = odd_bytes(ws[k]);
-                        mnE[k] = pk_min16(mnE[k], e);
-                        mnO[k] = pk_min16(mnO[k], o);
-                        mxE[k] = pk_max16(mxE[k], e);
-                        mxO[k] = pk_max16(mxO[k], o);
-                    }
-                }
+        for (int yy = 0; yy < 4; ++yy) {
+            if (yy < yn) {
+                const int64_t off = ((int64_t)(z0 + zz) * ny + (y0 + yy)) * nx + xp;
+                if constexpr (sizeof(T) == 1)
+                    c.add(load16_nt(vol + off));
+                else
+                    c.add(load16_nt(vol + off), load16_nt(vol + off + 8));
             }
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint32_t a = pk_min16(mnE[k], mnO[k]);
-            const uint32_t b = pk_max16(mxE[k], mxO[k]);
-            r.mn[k] = umin(lo16(a), hi16(a));
-            r.mx[k] = umax(lo16(b), hi16(b));
-        }
-    } else {
-        // u16: each 32-bit word holds 2 voxels; 2 words per brick row
-        uint32_t mn[4], mx[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) { mn[k] = 0xFFFFFFFFu; mx[k] = 0u; }
-        for (int zz = 0; zz < zn; ++zz) {
-#pragma unroll
-            for (int yy = 0; yy < 4; ++yy) {
-                if (yy < yn) {
-                    const int64_t off = ((int64_t)(z0 + zz) * ny + (y0 + yy)) * nx + x0;
-                    const uint4 a = load16(vol + off), b = load16(vol + off + 8);
-                    const uint32_t ws[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        mn[k] = pk_min16(mn[k], pk_min16(ws[2 * k], ws[2 * k + 1]));
-                        mx[k] = pk_max16(mx[k], pk_max16(ws[2 * k], ws[2 * k + 1]));
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            r.mn[k] = umin(lo16(mn[k]), hi16(mn[k]));
-            r.mx[k] = umax(lo16(mx[k]), hi16(mx[k]));
         }
     }
-    return r;
+    if constexpr (EDGE) {
+        if (xp != x0) c.shift(x0 - xp);
+    }
+    return c.bricks();
 }
 
-// Brick [min,max] of the quad.  FAST_EDGES: quads at the volume's edges (a
-// brick layer cut in z or y, 16 voxels that run past the row end) take the
-// unrolled paths above; otherwise compact looped ones, for a caller whose
-// register budget must stay that of the whole-quad path (with the unrolled
-// edge paths inlined, the compiler schedules the plain x pass for 190
-// registers instead of 97, which halves its occupancy on whole rows).
-template <typename T, bool FAST_EDGES = true, typename VP>
+// Brick [min,max] of the quad.  EDGES: how quads at the volume's edges (a brick
+// layer cut in z or y, 16 voxels that run past the row end) are read.
+//   kFast     unrolled paths, every load before the first use
+//   kCompact  the same at the row end, but cut layers row by row: for a caller
+//             whose register budget must stay that of the whole-quad path
+//             (with every unrolled path inlined, the compiler schedules the
+//             plain x pass for 190 registers instead of 97, which halves its
+//             occupancy on whole rows)
+//   kNoRowEnd as kCompact, for rows of a multiple of 16 voxels: no quad runs
+//             past the row end (with that path inlined as well, the plain x
+//             pass took 102 registers instead of 91 and 1% longer on the
+//             1024x1024x795 volume)
+enum QuadEdges { kFast, kCompact, kNoRowEnd };
+
+template <typename T, QuadEdges EDGES = kFast, typename VP>
 __device__ __forceinline__ QuadMinMax<T> quad_minmax(VP __restrict__ vol, int nx, int ny, int nz,
                                                      int q, int by, int bz) {
     const int x0 = 16 * q;
     const int z0 = 4 * bz, y0 = 4 * by;
     const int zn = min(4, nz - z0), yn = min(4, ny - y0);
-    if (x0 + 16 <= nx) {
-        if (zn == 4 && yn == 4) return quad_whole_rows<T, false>(vol, nx, ny, z0, y0, zn, yn, x0);
-        if constexpr (FAST_EDGES)
-            return quad_whole_rows<T, true>(vol, nx, ny, z0, y0, zn, yn, x0);
+    constexpr bool kRowEnd = EDGES != kNoRowEnd;
+    if (!kRowEnd || nx >= 16) {
+        if (zn == 4 && yn == 4)
+            return quad_whole_rows<T, false, kRowEnd>(vol, nx, ny, z0, y0, zn, yn, x0);
+        if constexpr (EDGES == kFast)
+            return quad_whole_rows<T, true, kRowEnd>(vol, nx, ny, z0, y0, zn, yn, x0);
         else
-            return quad_rows_looped<T>(vol, nx, ny, z0, y0, zn, yn, x0);
+            return quad_rows_looped<T, kRowEnd>(vol, nx, ny, z0, y0, zn, yn, x0);
     }
-    if constexpr (FAST_EDGES) {
+    if constexpr (EDGES == kFast) {
         if (nx >= 4) return quad_ragged_rows<T>(vol, nx, ny, z0, y0, zn, yn, x0);
     }
-    // one voxel at a time (rows of fewer than 4 voxels; or ragged rows when
-    // not FAST_EDGES)
+    // one voxel at a time (rows of fewer than 4 voxels; under 16 when not kFast)
     QuadMinMax<T> r;
 #pragma unroll
     for (int k = 0; k < 4; ++k) { r.mn[k] = 0xFFFFFFFFu; r.mx[k] = 0u; }
@@ -676,7 +726,7 @@ __device__ __forceinline__ bool any_alpha(const uint32_t* __restrict__ words,
         return any_bit(words, pre, lo, hi);
 }
 
-template <typename T, bool RUNS>
+template <typename T, bool RUNS, QuadEdges EDGES>
 __global__ void __launch_bounds__(256) k_plain_x(const T* __restrict__ vol, int nx, int ny, int nz,
                                                  int Bx, int By, int64_t rows, AlphaBits bits,
                                                  int nwords, int levels, uint8_t* __restrict__ dist,
@@ -692,7 +742,7 @@ __global__ void __launch_bounds__(256) k_plain_x(const T* __restrict__ vol, int 
     // the first segment's voxels are requested before the bitmap set-up, so
     // the loads are in flight while the block fills LDS
     QuadMinMax<T> r0;
-    if (live && 4 * lane < Bx) r0 = quad_minmax<T, false>(vol, nx, ny, nz, lane, by, bz);
+    if (live && 4 * lane < Bx) r0 = quad_minmax<T, EDGES>(vol, nx, ny, nz, lane, by, bz);
     for (int i = threadIdx.x; i < nwords; i += blockDim.x) s_words[i] = bits.w[i];
     for (int i = threadIdx.x; i <= nwords; i += blockDim.x) s_pre[i] = bits.pre[i];
     __syncthreads();
@@ -706,7 +756,7 @@ __global__ void __launch_bounds__(256) k_plain_x(const T* __restrict__ vol, int 
         const int q = s * kWave + lane;  // quad index within the row
         uint32_t o = 0;
         if (4 * q < Bx) {
-            const QuadMinMax<T> r = s == 0 ? r0 : quad_minmax<T, false>(vol, nx, ny, nz, q, by, bz);
+            const QuadMinMax<T> r = s == 0 ? r0 : quad_minmax<T, EDGES>(vol, nx, ny, nz, q, by, bz);
             const int nb = min(4, Bx - 4 * q);
             for (int k = 0; k < 4; ++k)
                 if (k < nb && any_alpha<RUNS>(s_words, s_pre, nwords, umin(r.mn[k], top), umin(r.mx[k], top)))
@@ -2122,7 +2172,7 @@ __device__ __forceinline__ void batch_scan_item(const BatchVol* __restrict__ vol
     }
 }
 
-__global__ void __launch_bounds__(kWave) k_batch_rows(const BatchVol* __restrict__ vols, int count,
+__global__ void __launch_bounds__(kWave, 4) k_batch_rows(const BatchVol* __restrict__ vols, int count,
                                                       int64_t total) {
     const int64_t t = xcd_item(blockIdx.x);
     if (t < total) batch_rows_item(vols, count, t);
@@ -2312,18 +2362,21 @@ hipError_t launch_plain_x(const PlainArgs& a, const AlphaBits& bits, hipStream_t
     const int64_t rows = (int64_t)a.By * a.Bz;
     const unsigned nb = blocks_for(rows, 4);
     // run lists only above 16384 levels, so only for 16-bit volumes
-    if (a.bytes == 1)
-        k_plain_x<uint8_t, false><<<nb, 256, 0, s>>>((const uint8_t*)a.vol, a.nx, a.ny, a.nz, a.Bx,
-                                                     a.By, rows, bits, a.nwords, a.levels, a.dist,
-                                                     a.store_vec);
+#define PDM_LAUNCH_PLAIN(T, RUNS, EDGES)                                                            \
+    k_plain_x<T, RUNS, EDGES><<<nb, 256, 0, s>>>((const T*)a.vol, a.nx, a.ny, a.nz, a.Bx, a.By, rows, \
+                                                 bits, a.nwords, a.levels, a.dist, a.store_vec)
+    const bool row_end = a.nx % 16 != 0;
+    if (a.bytes == 1 && row_end)
+        PDM_LAUNCH_PLAIN(uint8_t, false, kCompact);
+    else if (a.bytes == 1)
+        PDM_LAUNCH_PLAIN(uint8_t, false, kNoRowEnd);
+    else if (!a.runs && row_end)
+        PDM_LAUNCH_PLAIN(uint16_t, false, kCompact);
     else if (!a.runs)
-        k_plain_x<uint16_t, false><<<nb, 256, 0, s>>>((const uint16_t*)a.vol, a.nx, a.ny, a.nz, a.Bx,
-                                                      a.By, rows, bits, a.nwords, a.levels, a.dist,
-                                                      a.store_vec);
+        PDM_LAUNCH_PLAIN(uint16_t, false, kNoRowEnd);
     else
-        k_plain_x<uint16_t, true><<<nb, 256, 0, s>>>((const uint16_t*)a.vol, a.nx, a.ny, a.nz, a.Bx,
-                                                     a.By, rows, bits, a.nwords, a.levels, a.dist,
-                                                     a.store_vec);
+        PDM_LAUNCH_PLAIN(uint16_t, true, kCompact);
+#undef PDM_LAUNCH_PLAIN
     return hipGetLastError();
 }
 
