@@ -488,42 +488,126 @@ __device__ __forceinline__ uint32_t x_distances(uint32_t o, int lane, int xs, in
     return packed;
 }
 
-// Distances along x for short rows packed into one wave: lane L holds the
-// occupancy nibble of bricks 4r .. 4r+3 (r = L mod W) of the wave's row
-// floor(L / W), W a power of two from 1 to 64; a row has at most 4W bricks
-// and nothing outside it counts.  Returns the 4 clamped distances packed into
-// bytes.  Must be called by the whole wave.
-__device__ __forceinline__ uint32_t x_distances_rows(uint32_t o, int lane, int W) {
-    const uint64_t any = __ballot(o != 0u);
-    if (any == 0ull) return 0xFFFFFFFFu;  // no occupied brick in these rows
-    const int base = lane & ~(W - 1);
-    const uint64_t seg = W >= kWave ? ~0ull : (((1ull << W) - 1ull) << base);
-    const uint64_t mine = any & seg;
-    const uint64_t below = mine & ((1ull << lane) - 1ull);
-    const uint64_t above = (lane == kWave - 1) ? 0ull : (mine & (~0ull << (lane + 1)));
-    const int hik = o ? 31 - __clz(o) : 0;
-    const int lok = o ? __ffs(o) - 1 : 0;
-    const int src_l = below ? 63 - __clzll((long long)below) : lane;
-    const int src_r = above ? __ffsll((unsigned long long)above) - 1 : lane;
-    const int hi_l = __shfl(hik, src_l, kWave);
-    const int lo_r = __shfl(lok, src_r, kWave);
-    const int r = lane - base;
-    const int left_lane = below ? 4 * (src_l - base) + hi_l : -kNone;
-    const int right_lane = above ? 4 * (src_r - base) + lo_r : kNone;
-    uint32_t packed = 0;
+// Rows of at most 256 bricks in a wave: W lanes per row (the power of two with
+// 4W >= Bx, at most 64), 64/W rows side by side; lane L holds bricks 4q ..
+// 4q+3 (q = L mod W) of row floor(L / W).
+//
+// What one lane's four bricks say by themselves, by occupancy nibble: their
+// distances to the nearest occupied brick of the lane (bytes 0, 2 and 1, 3 as
+// 16-bit pairs, 255 for none), and the lane's last and first occupied brick
+// (kNoBrick away for none).
+struct NibbleEntry {
+    uint32_t e, o;
+    int last, first;
+};
+constexpr int kNoBrick = 8192;  // farther than any row; sums stay below 2^15
+
+// Fills the 16 entries (threads 0 .. 15; the caller synchronises).
+__device__ __forceinline__ void fill_nibbles(NibbleEntry* t) {
+    const int nib = threadIdx.x;
+    if (nib >= 16) return;
+    uint32_t d[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const int x = 4 * r + k;
-        const uint32_t ml = o & ((2u << k) - 1u);
-        const uint32_t mr = o & (0xFu & ~((1u << k) - 1u));
-        const int lp = ml ? 4 * r + (31 - __clz(ml)) : left_lane;
-        const int rp = mr ? 4 * r + (__ffs(mr) - 1) : right_lane;
-        int d = min(x - lp, rp - x);
-        d = min(d, 255);
-        packed |= (uint32_t)d << (8 * k);
+        d[k] = 255u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if ((nib >> j) & 1) d[k] = umin(d[k], (uint32_t)(j < k ? k - j : j - k));
     }
-    return packed;
+    t[nib] = {d[0] | (d[2] << 16), d[1] | (d[3] << 16), nib ? 31 - __clz(nib) : -kNoBrick,
+              nib ? __ffs(nib) - 1 : kNoBrick};
 }
+
+// The other lanes of a lane's row to its left and right, as lane masks.
+struct RowMasks {
+    uint64_t left, right;
+
+    __device__ __forceinline__ RowMasks(int lane, int W) {
+        const int base = lane & ~(W - 1);
+        const uint64_t seg = W >= kWave ? ~0ull : (((1ull << W) - 1ull) << base);
+        left = seg & ((1ull << lane) - 1ull);
+        right = lane == kWave - 1 ? 0ull : seg & (~0ull << (lane + 1));
+    }
+};
+
+// The 4 distances of every lane, clamped, packed into bytes; nothing outside a
+// row counts.  o: occupancy nibble.  Must be called by the whole wave.  The
+// lane's own bricks come from the table; the nearest occupied brick on either
+// side is that of the nearest lane with one (one ballot, one cross-lane read
+// per side), and one minimum of three takes the four distances two at a time:
+// half the instructions of a distance at a time (k_pom_x on the 128x128x115
+// grid, 32 partitions, dense: 50 -> 34 us; 64 partitions of 256x256x199 mostly
+// empty rows: 197 -> 174).
+__device__ __forceinline__ uint32_t x_distances_rows(uint32_t o, int lane, const RowMasks& m,
+                                                     const NibbleEntry* __restrict__ table) {
+    const uint64_t any = __ballot(o != 0u);
+    if (any == 0ull) return 0xFFFFFFFFu;  // no occupied brick in these rows
+    const NibbleEntry n = table[o];
+    const uint64_t l = any & m.left, r = any & m.right;
+    const int src_l = 63 - __clzll((long long)l), src_r = __ffsll((unsigned long long)r) - 1;
+    // the nearest occupied brick's position, counted from the lane's first brick
+    const int last = __builtin_amdgcn_ds_bpermute(src_l << 2, n.last);
+    const int first = __builtin_amdgcn_ds_bpermute(src_r << 2, n.first);
+    const int dl = l ? 4 * (lane - src_l) - last : kNoBrick;          // from brick 0
+    const int dr = r ? 4 * (src_r - lane) + first - 3 : kNoBrick;     // from brick 3
+    const uint32_t dl2 = (uint32_t)dl | ((uint32_t)dl << 16), dr2 = (uint32_t)dr | ((uint32_t)dr << 16);
+    const uint32_t e = pk_min16(pk_min16(n.e, pk_add16(dl2, 0x00020000u)), pk_add16(dr2, 0x00010003u));
+    const uint32_t d = pk_min16(pk_min16(n.o, pk_add16(dl2, 0x00030001u)), pk_add16(dr2, 0x00000002u));
+    return e | (d << 8);
+}
+
+// [min,max] of a lane's 4 bricks as 16-bit pairs (bricks 0, 2 and 1, 3).
+struct RangeQuad {
+    uint32_t mnE, mnO, mxE, mxO;
+
+    __device__ __forceinline__ RangeQuad(const uint32_t (&mn)[4], const uint32_t (&mx)[4])
+        : mnE(lo16(mn[0]) | (mn[2] << 16)), mnO(lo16(mn[1]) | (mn[3] << 16)),
+          mxE(lo16(mx[0]) | (mx[2] << 16)), mxO(lo16(mx[1]) | (mx[3] << 16)) {}
+    // bit k: [min,max] of brick k meets [lo, hi] (bits outside `valid` are 0)
+    __device__ __forceinline__ uint32_t meets(uint32_t lo, uint32_t hi, uint32_t valid) const {
+        const uint32_t lo2 = lo | (lo << 16), hi2 = hi | (hi << 16);
+        // 0 where min <= hi and max >= lo
+        const uint32_t tE = pk_sub_sat16(mnE, hi2) | pk_sub_sat16(lo2, mxE);
+        const uint32_t tO = pk_sub_sat16(mnO, hi2) | pk_sub_sat16(lo2, mxO);
+        const uint32_t x = pk_sub_sat16(0x00010001u, tE) | (pk_sub_sat16(0x00010001u, tO) << 1);
+        return (x | (x >> 14)) & valid;
+    }
+};
+
+// Where a lane's packed distances go: rows of a wave's 64/W rows, through a
+// buffer that covers these rows of one map.  A quad cut by the row end is
+// stored as the row's last 4 bytes (its first bytes are the lane before's, the
+// same values); lanes without bricks lie past the buffer, where stores are
+// dropped.  Rows of fewer than 4 bricks are stored byte by byte.
+struct RowStore {
+    int voff, shift, nb, Bx;
+    bool cut;
+
+    __device__ __forceinline__ RowStore(int lane, int W, int Bx_) {
+        const int q = lane & (W - 1);
+        Bx = Bx_;
+        nb = max(0, min(4, Bx - 4 * q));
+        cut = nb > 0 && nb < 4;
+        shift = cut ? 8 * (4 - nb) : 0;
+        voff = nb > 0 ? (lane / W) * Bx + 4 * q - (Bx >= 4 ? shift / 8 : 0) : -4;
+    }
+    // rows_left: rows from the wave's first to the map's last
+    template <typename P>
+    __device__ __forceinline__ void store(P first_row, int64_t rows_left, int per, uint32_t packed) const {
+        const int records = (int)(rows_left < per ? rows_left : per) * Bx;
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc((uint8_t*)first_row, (short)0, records, 0x00020000);
+        if (Bx >= 4) {
+            const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)packed, 0x138, 0xf, 0xf, true);
+            const uint32_t w = cut ? (uint32_t)((((uint64_t)packed << 32) | prev) >> (32 - shift)) : packed;
+            __builtin_amdgcn_raw_buffer_store_b32(w, rs, voff, 0, 0);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(packed >> (8 * k)), rs, k < nb ? voff + k : -4, 0, 0);
+        }
+    }
+};
 
 // Position of the first / last occupied brick of a segment (wave-uniform).
 __device__ __forceinline__ int seg_first(uint32_t o, int xs) {
@@ -583,26 +667,30 @@ __device__ __forceinline__ void wave_value_range(const uint32_t (&mn)[4], const 
 }
 
 // ---------------------------------------------------------------------------
-// k_pom_x: one wave per brick row (bz, by); 4 waves per work-group.  For
-// every partition p: POM nibble from [min,max] (RANGE reading) and the x
-// distances, written to pdms[p*G + row*Bx + x].  Rows of at most 128 bricks
-// are packed 64/W to a wave (W < 64 lanes per row, the power of two with
-// 4W >= Bx), so narrow grids keep every lane busy.
+// k_pom_x: 4 waves per work-group, 64/W brick rows (bz, by) to a wave (rows of
+// at most 256 bricks; longer ones a wave each).  For every partition p: POM
+// nibble from [min,max] (RANGE reading) and the x distances, written to
+// pdms[p*G + row*Bx + x].
 // ---------------------------------------------------------------------------
 template <typename T>
 __global__ void __launch_bounds__(256) k_pom_x(const T* __restrict__ bmin,
                                                const T* __restrict__ bmax, int Bx, int64_t rows,
                                                Bounds bounds, int n, uint8_t* __restrict__ pdms,
                                                int64_t G, int store_vec, int W) {
+    __shared__ NibbleEntry nibbles[16];
+    fill_nibbles(nibbles);
+    __syncthreads();
     const int lane = threadIdx.x & (kWave - 1);
-    if (W < kWave) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (Bx <= kSegBricks) {
         const int per = kWave / W;
-        const int64_t row0 = ((int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave)) * per;
+        const int64_t row0 = ((int64_t)blockIdx.x * (blockDim.x / kWave) + wave) * per;
         if (row0 >= rows) return;  // wave-uniform
+        const RowStore out(lane, W, Bx);
+        const RowMasks masks(lane, W);
         const int64_t row = row0 + lane / W;
-        const int q = lane & (W - 1);
-        const int nb = row < rows ? max(0, min(4, Bx - 4 * q)) : 0;
-        const int64_t rbase = row * Bx + 4 * q;
+        const int nb = row < rows ? out.nb : 0;
+        const int64_t rbase = row * Bx + 4 * (lane & (W - 1));
         uint32_t mn[4], mx[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -611,46 +699,23 @@ __global__ void __launch_bounds__(256) k_pom_x(const T* __restrict__ bmin,
         }
         uint32_t wmin, wmax;
         wave_value_range(mn, mx, wmin, wmax);
+        const RangeQuad range(mn, mx);
+        const uint32_t valid = (1u << nb) - 1u;
+        uint8_t* dst = pdms + row0 * Bx;
         for (int p = 0; p < n; ++p) {
             const uint32_t lo = (uint32_t)bounds.b[p], hi = (uint32_t)bounds.b[p + 1] - 1u;
             uint32_t packed = 0xFFFFFFFFu;
-            if (hi >= wmin && lo <= wmax) {
-                uint32_t o = 0;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) o |= (mn[k] <= hi && mx[k] >= lo) ? (1u << k) : 0u;
-                packed = x_distances_rows(o, lane, W);
-            }
-            if (nb > 0) store_quad(pdms + (int64_t)p * G, rbase, nb, packed, store_vec);
+            if (hi >= wmin && lo <= wmax)
+                packed = x_distances_rows(range.meets(lo, hi, valid), lane, masks, nibbles);
+            out.store(dst, rows - row0, per, packed);
+            dst += G;
         }
         return;
     }
-    const int64_t row = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
+    const int64_t row = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave;
     if (row >= rows) return;  // wave-uniform
     const int nseg = (Bx + kSegBricks - 1) / kSegBricks;
     const int64_t rbase = row * Bx;
-    if (nseg == 1) {
-        uint32_t mn[4], mx[4];
-        const int nb = max(0, min(4, Bx - 4 * lane));
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            mn[k] = k < nb ? (uint32_t)bmin[rbase + 4 * lane + k] : 0xFFFFFFFFu;
-            mx[k] = k < nb ? (uint32_t)bmax[rbase + 4 * lane + k] : 0u;
-        }
-        uint32_t wmin, wmax;
-        wave_value_range(mn, mx, wmin, wmax);
-        for (int p = 0; p < n; ++p) {
-            const uint32_t lo = (uint32_t)bounds.b[p], hi = (uint32_t)bounds.b[p + 1] - 1u;
-            uint32_t packed = 0xFFFFFFFFu;
-            if (hi >= wmin && lo <= wmax) {
-                uint32_t o = 0;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) o |= (mn[k] <= hi && mx[k] >= lo) ? (1u << k) : 0u;
-                packed = x_distances(o, lane, 0, -kNone, kNone);
-            }
-            if (nb > 0) store_quad(pdms + (int64_t)p * G, rbase + 4 * lane, nb, packed, store_vec);
-        }
-        return;
-    }
     // long rows: segments of 256 bricks; only the neighbouring segments can
     // hold a brick within the cap
     auto nibble = [&](int seg, uint32_t lo, uint32_t hi) -> uint32_t {
@@ -825,8 +890,10 @@ __global__ void __launch_bounds__(256) k_plain_cached_x(const T* __restrict__ bm
                                                         int store_vec, int W, int load_vec) {
     __shared__ uint32_t s_words[PDM_ALPHA_WORDS];
     __shared__ uint16_t s_pre[PDM_ALPHA_WORDS + 1];
+    __shared__ NibbleEntry nibbles[16];
     for (int i = threadIdx.x; i < nwords; i += blockDim.x) s_words[i] = bits.w[i];
     for (int i = threadIdx.x; i <= nwords; i += blockDim.x) s_pre[i] = bits.pre[i];
+    fill_nibbles(nibbles);
     __syncthreads();
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t top = (uint32_t)levels - 1u;
@@ -845,6 +912,7 @@ __global__ void __launch_bounds__(256) k_plain_cached_x(const T* __restrict__ bm
         const int64_t row0 = wave * per * kCachedPasses;
         if (row0 >= rows) return;  // wave-uniform
         const int q = lane & (W - 1);
+        const RowMasks masks(lane, W);
         Quad<T> mn[kCachedPasses], mx[kCachedPasses];
         int nb[kCachedPasses];
 #pragma unroll
@@ -858,7 +926,7 @@ __global__ void __launch_bounds__(256) k_plain_cached_x(const T* __restrict__ bm
 #pragma unroll
         for (int j = 0; j < kCachedPasses; ++j) {
             const int64_t row = row0 + (int64_t)j * per + lane / W;
-            const uint32_t packed = x_distances_rows(nibble(mn[j], mx[j], nb[j]), lane, W);
+            const uint32_t packed = x_distances_rows(nibble(mn[j], mx[j], nb[j]), lane, masks, nibbles);
             if (nb[j] > 0) store_quad(dist, row * Bx + 4 * q, nb[j], packed, store_vec);
         }
         return;
@@ -892,40 +960,89 @@ __global__ void __launch_bounds__(256) k_plain_cached_x(const T* __restrict__ bm
 // literal POM wording of Sec. 3.1), for the PDM build and the plain method.
 // ---------------------------------------------------------------------------
 
-// Calls f(k, value) for every voxel of the 4 bricks x = 4q..4q+3 of brick row
-// (bz, by) that lies inside the volume (k = brick within the quad).
-template <typename T, typename F>
+// Calls f(k, value) for the voxels of the 4 bricks x = 4q..4q+3 of brick row
+// (bz, by) that lie inside the volume (k = brick within the quad), each at
+// least once; values of bricks outside the grid are unspecified.  Rows past
+// the volume's end in z or y repeat its last row, and a quad that runs past the
+// row end takes the row's last 16 voxels moved up to its own, the row's last
+// voxel after them: the same loads for every lane of the wave.  ROW_END: rows
+// may be no multiple of 16 voxels.  AHEAD: the next slice's rows are loaded
+// while one is looked up, for twice the registers: the EXACT POM pass, few
+// waves with much work each (509x487x451 u16: 108 -> 58 us with the row end
+// above), but not the plain pass, which streams (512x512x460 u16: 77 against
+// 88 us).
+template <typename T, bool ROW_END, bool AHEAD, typename F>
 __device__ __forceinline__ void quad_voxels(const T* __restrict__ vol, int nx, int ny, int nz, int q,
                                             int by, int bz, F f) {
     const int x0 = 16 * q;
     const int z0 = 4 * bz, y0 = 4 * by;
     const int zn = min(4, nz - z0), yn = min(4, ny - y0);
-    if (x0 + 16 <= nx) {
+    constexpr int kWords = 4 * (int)sizeof(T);  // 16 voxels
+    auto lookup = [&](const uint32_t (&w)[kWords]) {
+#pragma unroll
+        for (int i = 0; i < kWords; ++i) {
+            const int k = i / (int)sizeof(T);
+            if constexpr (sizeof(T) == 1) {
+#pragma unroll
+                for (int b = 0; b < 4; ++b) f(k, (w[i] >> (8 * b)) & 0xFFu);
+            } else {
+                f(k, lo16(w[i]));
+                f(k, hi16(w[i]));
+            }
+        }
+    };
+    auto load = [&](int64_t off, uint32_t (&t)[kWords]) {
+#pragma unroll
+        for (int i = 0; i < kWords / 4; ++i) {
+            const uint4 a = load16(vol + off + i * (16 / (int)sizeof(T)));
+            t[4 * i] = a.x;
+            t[4 * i + 1] = a.y;
+            t[4 * i + 2] = a.z;
+            t[4 * i + 3] = a.w;
+        }
+    };
+    if constexpr (!ROW_END) {  // row by row: fewest registers
         for (int zz = 0; zz < zn; ++zz) {
 #pragma unroll
             for (int yy = 0; yy < 4; ++yy) {
                 if (yy < yn) {
-                    const int64_t off = ((int64_t)(z0 + zz) * ny + (y0 + yy)) * nx + x0;
-                    if constexpr (sizeof(T) == 1) {
-                        const uint4 w = load16(vol + off);
-                        const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-                        for (int k = 0; k < 4; ++k)
-#pragma unroll
-                            for (int b = 0; b < 4; ++b) f(k, (ws[k] >> (8 * b)) & 0xFFu);
-                    } else {
-                        const uint4 a = load16(vol + off), c = load16(vol + off + 8);
-                        const uint32_t ws[8] = {a.x, a.y, a.z, a.w, c.x, c.y, c.z, c.w};
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            f(k, lo16(ws[2 * k]));
-                            f(k, hi16(ws[2 * k]));
-                            f(k, lo16(ws[2 * k + 1]));
-                            f(k, hi16(ws[2 * k + 1]));
-                        }
-                    }
+                    uint32_t w[kWords];
+                    load(((int64_t)(z0 + zz) * ny + (y0 + yy)) * nx + x0, w);
+                    lookup(w);
                 }
             }
+        }
+    } else if (nx >= 16) {
+        const int xp = min(x0, nx - 16);
+        uint32_t w[4][kWords], next[4][kWords];
+        auto load_slice = [&](int zz, uint32_t (&t)[4][kWords]) {
+#pragma unroll
+            for (int yy = 0; yy < 4; ++yy)
+                load(((int64_t)(z0 + min(zz, zn - 1)) * ny + (y0 + min(yy, yn - 1))) * nx + xp, t[yy]);
+        };
+        if (AHEAD) load_slice(0, w);
+#pragma unroll 1
+        for (int zz = 0; zz < 4; ++zz) {
+            if (AHEAD) {
+                load_slice(min(zz + 1, 3), next);
+                __builtin_amdgcn_sched_barrier(0);  // the loads ahead of the lookups
+            } else {
+                load_slice(zz, w);
+            }
+#pragma unroll
+            for (int yy = 0; yy < 4; ++yy) {
+                if (xp != x0) {
+                    const uint32_t last = w[yy][kWords - 1];
+                    shift_voxels<(int)sizeof(T)>(w[yy], x0 - xp, sizeof(T) == 1 ? (last >> 24) * 0x01010101u
+                                                                                : (last >> 16) * 0x00010001u);
+                }
+                lookup(w[yy]);
+            }
+#pragma unroll
+            for (int yy = 0; yy < 4; ++yy)
+#pragma unroll
+                for (int i = 0; i < kWords; ++i)
+                    if (AHEAD) w[yy][i] = next[yy][i];
         }
     } else {
         const int xn = min(16, nx - x0);
@@ -945,30 +1062,30 @@ __device__ __forceinline__ void quad_voxels(const T* __restrict__ vol, int nx, i
 // its 4 bricks, which partitions hold one of their voxels (NW = ceil(n/32)
 // mask words per brick, from an LDS table intensity -> partition), then the
 // wave computes every partition's x distances from those masks.  Reads the
-// volume once and writes n*G bytes.  Rows of at most 128 bricks are packed
-// 64/W to a wave (W lanes per row), as in k_pom_x.
-template <typename T, int NW, bool PACK>
+// volume once and writes n*G bytes.  64/W rows to a wave, as in k_pom_x.
+template <typename T, int NW>
 __global__ void __launch_bounds__(256) k_pom_exact_x(const T* __restrict__ vol, int nx, int ny,
                                                      int nz, int Bx, int By, int64_t rows,
                                                      Bounds bounds, int n, int levels,
-                                                     uint8_t* __restrict__ pdms, int64_t G,
-                                                     int store_vec, int W) {
+                                                     uint8_t* __restrict__ pdms, int64_t G, int W) {
     __shared__ uint8_t s_part[PDM_EXACT_MAX_LEVELS];
-    // partition p paints its intensities [bounds[p], bounds[p+1])
-    for (int p = threadIdx.x; p < n; p += blockDim.x)
-        for (int v = bounds.b[p]; v < bounds.b[p + 1]; ++v) s_part[v] = (uint8_t)p;
+    __shared__ NibbleEntry nibbles[16];
+    // 256/n threads paint a partition's intensities [bounds[p], bounds[p+1])
+    const int share = (int)blockDim.x / n, part = (int)threadIdx.x / share;
+    if (part < n)
+        for (int v = bounds.b[part] + (int)threadIdx.x % share; v < bounds.b[part + 1]; v += share)
+            s_part[v] = (uint8_t)part;
+    fill_nibbles(nibbles);
     __syncthreads();
     const int lane = threadIdx.x & (kWave - 1);
-    // PACK (W < 64): rows of at most 128 bricks, 64/W to a wave (W lanes per row)
-    if (!PACK) W = kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int per = kWave / W;
-    const int64_t row0 = ((int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave)) * per;
+    const int64_t row0 = ((int64_t)blockIdx.x * (blockDim.x / kWave) + wave) * per;
     if (row0 >= rows) return;  // wave-uniform, after the barrier
     const int64_t row = row0 + lane / W;
     const int q = lane & (W - 1);  // quad index within the row
     const bool row_ok = row < rows;
     const int by = row_ok ? (int)(row % By) : 0, bz = row_ok ? (int)(row / By) : 0;
-    const int64_t rbase = row * Bx;
     uint32_t mk[4][NW];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
@@ -976,14 +1093,16 @@ __global__ void __launch_bounds__(256) k_pom_exact_x(const T* __restrict__ vol, 
         for (int w = 0; w < NW; ++w) mk[k][w] = 0u;
     const uint32_t top = (uint32_t)levels - 1u;  // voxels >= levels break the precondition
     if (row_ok && 4 * q < Bx) {
-        quad_voxels<T>(vol, nx, ny, nz, q, by, bz, [&](int k, uint32_t val) {
+        quad_voxels<T, true, true>(vol, nx, ny, nz, q, by, bz, [&](int k, uint32_t val) {
             const uint32_t pid = s_part[umin(val, top)];
             const uint32_t bit = 1u << (pid & 31u);
 #pragma unroll
             for (int w = 0; w < NW; ++w) mk[k][w] |= ((pid >> 5) == (uint32_t)w) ? bit : 0u;
         });
     }
-    const int nb = row_ok ? max(0, min(4, Bx - 4 * q)) : 0;
+    const RowStore out(lane, W, Bx);
+    const RowMasks masks(lane, W);
+    uint8_t* dst = pdms + row0 * Bx;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
         const int pend = min(32, n - 32 * w);
@@ -991,13 +1110,8 @@ __global__ void __launch_bounds__(256) k_pom_exact_x(const T* __restrict__ vol, 
             uint32_t o = 0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) o |= ((mk[k][w] >> b) & 1u) << k;
-            uint32_t packed;
-            if constexpr (PACK)
-                packed = x_distances_rows(o, lane, W);
-            else
-                packed = x_distances(o, lane, 0, -kNone, kNone);
-            if (nb > 0)
-                store_quad(pdms + (int64_t)(32 * w + b) * G, rbase + 4 * q, nb, packed, store_vec);
+            out.store(dst, rows - row0, per, x_distances_rows(o, lane, masks, nibbles));
+            dst += G;
         }
     }
 }
@@ -1005,7 +1119,7 @@ __global__ void __launch_bounds__(256) k_pom_exact_x(const T* __restrict__ vol, 
 // k_plain_exact_x: the plain method's occupancy in the EXACT reading (some
 // voxel of the brick has alpha != 0, looked up in the LDS bitmap) and its x
 // distances; long rows in 256-brick segments as in k_plain_x.
-template <typename T>
+template <typename T, bool ROW_END>
 __global__ void __launch_bounds__(256) k_plain_exact_x(const T* __restrict__ vol, int nx, int ny,
                                                        int nz, int Bx, int By, int64_t rows,
                                                        AlphaBits bits, int nwords, int levels,
@@ -1027,7 +1141,7 @@ __global__ void __launch_bounds__(256) k_plain_exact_x(const T* __restrict__ vol
         const int q = s * kWave + lane;
         uint32_t o = 0;
         if (4 * q < Bx) {
-            quad_voxels<T>(vol, nx, ny, nz, q, by, bz, [&](int k, uint32_t val) {
+            quad_voxels<T, ROW_END, false>(vol, nx, ny, nz, q, by, bz, [&](int k, uint32_t val) {
                 const uint32_t v = umin(val, top);
                 o |= ((s_words[v >> 5] >> (v & 31u)) & 1u) << k;
             });
@@ -2073,7 +2187,8 @@ __device__ __forceinline__ int batch_volume_of(const BatchVol* __restrict__ vols
 // bricks takes W = row_lanes lanes (4 bricks each, W the power of two >=
 // Bx/4), so one wave pass covers 64/W rows.
 template <typename T>
-__device__ __forceinline__ void batch_rows(const BatchVol& d, int bz, int by0, int by1) {
+__device__ __forceinline__ void batch_rows(const BatchVol& d, int bz, int by0, int by1,
+                                           const NibbleEntry* __restrict__ nibbles) {
     const int lane = threadIdx.x;
     const PDM_GLB T* vol = (const PDM_GLB T*)d.vol;
     PDM_GLB T* bmin = (PDM_GLB T*)d.bmin;
@@ -2085,14 +2200,14 @@ __device__ __forceinline__ void batch_rows(const BatchVol& d, int bz, int by0, i
     const int W = d.row_lanes;
     const int n = d.n, Bx = d.Bx, By = d.By;
     const int64_t G = d.G;
-    const bool vec = d.store_vec != 0;
+    const RowStore out(lane, W, Bx);
+    const RowMasks masks(lane, W);
     const PDM_GLB int32_t* bounds = (const PDM_GLB int32_t*)d.bounds;
     const int q = lane & (W - 1);
     const int per = kWave / W;
-    const int nb_row = max(0, min(4, Bx - 4 * q));
     for (int row0 = by0; row0 < by1; row0 += per) {
         const int by = row0 + lane / W;
-        const int nb = by < by1 ? nb_row : 0;
+        const int nb = by < by1 ? out.nb : 0;
         const int64_t rbase = ((int64_t)bz * By + by) * Bx + 4 * q;
         uint32_t mn[4] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
         uint32_t mx[4] = {0u, 0u, 0u, 0u};
@@ -2117,33 +2232,33 @@ __device__ __forceinline__ void batch_rows(const BatchVol& d, int bz, int by0, i
         }
         uint32_t wmin, wmax;
         wave_value_range(mn, mx, wmin, wmax);
+        const RangeQuad range(mn, mx);
+        const uint32_t valid = (1u << nb) - 1u;
+        PDM_GLB uint8_t* dst = pdms + ((int64_t)bz * By + row0) * Bx;
         uint32_t lo = (uint32_t)bounds[0];
         for (int p = 0; p < n; ++p) {
             const uint32_t next = (uint32_t)bounds[p + 1], hi = next - 1u;
             uint32_t packed = 0xFFFFFFFFu;
-            if (hi >= wmin && lo <= wmax) {
-                uint32_t o = 0;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) o |= (mn[k] <= hi && mx[k] >= lo) ? (1u << k) : 0u;
-                packed = x_distances_rows(o, lane, W);
-            }
-            if (nb > 0) store_quad(pdms + (int64_t)p * G, rbase, nb, packed, vec);
+            if (hi >= wmin && lo <= wmax)
+                packed = x_distances_rows(range.meets(lo, hi, valid), lane, masks, nibbles);
+            out.store(dst, by1 - row0, per, packed);
+            dst += G;
             lo = next;
         }
     }
 }
 
 __device__ __forceinline__ void batch_rows_item(const BatchVol* __restrict__ vols, int count,
-                                                int64_t t) {
+                                                int64_t t, const NibbleEntry* __restrict__ nibbles) {
     const BatchVol& d = vols[batch_volume_of(vols, count, 0, t)];
     const int64_t local = t - d.first[0];
     const int bz = (int)(local / d.row_groups);
     const int by0 = (int)(local % d.row_groups) * d.rows;
     const int by1 = min(d.By, by0 + d.rows);
     if (d.bytes == 1)
-        batch_rows<uint8_t>(d, bz, by0, by1);
+        batch_rows<uint8_t>(d, bz, by0, by1, nibbles);
     else
-        batch_rows<uint16_t>(d, bz, by0, by1);
+        batch_rows<uint16_t>(d, bz, by0, by1, nibbles);
 }
 
 // ph 1: y passes, ph 2: z passes of one item (64*lines_mult lines).
@@ -2174,8 +2289,11 @@ __device__ __forceinline__ void batch_scan_item(const BatchVol* __restrict__ vol
 
 __global__ void __launch_bounds__(kWave, 4) k_batch_rows(const BatchVol* __restrict__ vols, int count,
                                                       int64_t total) {
+    __shared__ NibbleEntry nibbles[16];
+    fill_nibbles(nibbles);
+    __syncthreads();
     const int64_t t = xcd_item(blockIdx.x);
-    if (t < total) batch_rows_item(vols, count, t);
+    if (t < total) batch_rows_item(vols, count, t, nibbles);
 }
 
 __global__ void __launch_bounds__(kWave) k_batch_scan(const BatchVol* __restrict__ vols, int count,
@@ -2246,10 +2364,13 @@ __global__ void __launch_bounds__(kWave) k_batch_single(const BatchVol* __restri
                                                         int64_t total2, int lines_mult,
                                                         BatchSync* st, uint64_t limit_ticks) {
     extern __shared__ __align__(16) uint8_t tbl[];  // scan_table_bytes of the longest line
+    __shared__ NibbleEntry nibbles[16];
+    fill_nibbles(nibbles);
+    __syncthreads();
     for (;;) {
         const int64_t t = lane0_fetch_add(&st->ticket[0][0], 1u);
         if (t >= total0) break;
-        batch_rows_item(vols, count, t);
+        batch_rows_item(vols, count, t, nibbles);
     }
     if (!grid_barrier(st, 0u, limit_ticks)) return;
     for (;;) {
@@ -2411,17 +2532,9 @@ static hipError_t launch_pom_exact_t(const PomExactArgs& a, const Bounds& b, hip
     while (W < kWave && 4 * W < a.Bx) W *= 2;
     const unsigned nb = blocks_for(rows, 4 * (kWave / W));
     const int nw = (a.n + 31) / 32;
-#define PDM_LAUNCH_EXACT(NW)                                                                   \
-    do {                                                                                       \
-        if (W < kWave)                                                                         \
-            k_pom_exact_x<T, NW, true><<<nb, 256, 0, s>>>((const T*)a.vol, a.nx, a.ny, a.nz,     \
-                                                          a.Bx, a.By, rows, b, a.n, a.levels,    \
-                                                          a.pdms, a.G, a.store_vec, W);          \
-        else                                                                                   \
-            k_pom_exact_x<T, NW, false><<<nb, 256, 0, s>>>((const T*)a.vol, a.nx, a.ny, a.nz,    \
-                                                           a.Bx, a.By, rows, b, a.n, a.levels,   \
-                                                           a.pdms, a.G, a.store_vec, W);         \
-    } while (0)
+#define PDM_LAUNCH_EXACT(NW)                                                                     \
+    k_pom_exact_x<T, NW><<<nb, 256, 0, s>>>((const T*)a.vol, a.nx, a.ny, a.nz, a.Bx, a.By, rows, b, \
+                                            a.n, a.levels, a.pdms, a.G, W)
     if (nw == 1)
         PDM_LAUNCH_EXACT(1);
     else if (nw == 2)
@@ -2441,14 +2554,18 @@ hipError_t launch_pom_exact_x(const PomExactArgs& a, const Bounds& b, hipStream_
 hipError_t launch_plain_exact_x(const PlainArgs& a, const AlphaBits& bits, hipStream_t s) {
     const int64_t rows = (int64_t)a.By * a.Bz;
     const unsigned nb = blocks_for(rows, 4);
-    if (a.bytes == 1)
-        k_plain_exact_x<uint8_t><<<nb, 256, 0, s>>>((const uint8_t*)a.vol, a.nx, a.ny, a.nz, a.Bx,
-                                                    a.By, rows, bits, a.nwords, a.levels, a.dist,
-                                                    a.store_vec);
+#define PDM_LAUNCH_PLAIN_EXACT(T, ROW_END)                                                           \
+    k_plain_exact_x<T, ROW_END><<<nb, 256, 0, s>>>((const T*)a.vol, a.nx, a.ny, a.nz, a.Bx, a.By, rows, \
+                                                   bits, a.nwords, a.levels, a.dist, a.store_vec)
+    if (a.bytes == 1 && a.nx % 16 != 0)
+        PDM_LAUNCH_PLAIN_EXACT(uint8_t, true);
+    else if (a.bytes == 1)
+        PDM_LAUNCH_PLAIN_EXACT(uint8_t, false);
+    else if (a.nx % 16 != 0)
+        PDM_LAUNCH_PLAIN_EXACT(uint16_t, true);
     else
-        k_plain_exact_x<uint16_t><<<nb, 256, 0, s>>>((const uint16_t*)a.vol, a.nx, a.ny, a.nz, a.Bx,
-                                                     a.By, rows, bits, a.nwords, a.levels, a.dist,
-                                                     a.store_vec);
+        PDM_LAUNCH_PLAIN_EXACT(uint16_t, false);
+#undef PDM_LAUNCH_PLAIN_EXACT
     return hipGetLastError();
 }
 

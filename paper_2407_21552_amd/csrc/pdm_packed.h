@@ -17,6 +17,14 @@ __device__ __forceinline__ uint32_t pk_max16(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(us2, a),
                                                                   __builtin_bit_cast(us2, b)));
 }
+__device__ __forceinline__ uint32_t pk_add16(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(us2, a) + __builtin_bit_cast(us2, b));
+}
+// difference, 0 where b > a
+__device__ __forceinline__ uint32_t pk_sub_sat16(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(us2, a),
+                                                                      __builtin_bit_cast(us2, b)));
+}
 // bytes 0 and 2 of w in the two 16-bit halves
 __device__ __forceinline__ uint32_t even_bytes(uint32_t w) { return w & 0x00FF00FFu; }
 // bytes 1 and 3 of w in the two 16-bit halves
