@@ -126,15 +126,16 @@ pdm_status plain_args(const pdm_volume* v, const void* d_volume, const float* h_
     return PDM_OK;
 }
 
-// The second phase of the builds: x distances written by this library's own x
-// passes, which the sweeps may take (pdm_distance_yz takes any bytes).
+// The second phase of the builds and recomputes: x distances written by this
+// library's own x passes, which the sweeps and the slice pass may take
+// (pdm_distance_yz takes any bytes).
 pdm_status complete(const pdm_volume* v, uint8_t* d_maps, int32_t count, hipStream_t stream) {
     pdm_grid g;
     const pdm_status st = check_volume(v, &g);
     if (st != PDM_OK) return st;
     return from_hip(pdm::sweep_fits(count, g.bx, g.by, g.bz)
                         ? pdm::launch_sweep(d_maps, count, g.bx, g.by, g.bz, stream)
-                        : pdm::launch_distance_yz(d_maps, count, g.bx, g.by, g.bz, stream));
+                        : pdm::launch_distance_yz(d_maps, count, g.bx, g.by, g.bz, true, stream));
 }
 
 }  // namespace
@@ -213,7 +214,7 @@ pdm_status pdm_distance_yz(const pdm_volume* v, uint8_t* d_maps, int32_t count, 
     const pdm_status st = check_volume(v, &g);
     if (st != PDM_OK) return st;
     if (d_maps == nullptr || count < 1 || count > PDM_MAX_PARTITIONS) return PDM_E_INVAL;
-    return from_hip(pdm::launch_distance_yz(d_maps, count, g.bx, g.by, g.bz, stream));
+    return from_hip(pdm::launch_distance_yz(d_maps, count, g.bx, g.by, g.bz, false, stream));
 }
 
 pdm_status pdm_build_partitions(const pdm_volume* v, const void* d_bmin, const void* d_bmax,
@@ -594,7 +595,7 @@ pdm_status pdm_full_recompute(const pdm_volume* v, const void* d_volume, const f
                               uint8_t* d_dist, hipStream_t stream) {
     pdm_status st = pdm_plain_distance_x(v, d_volume, h_alpha, d_dist, stream);
     if (st != PDM_OK) return st;
-    return pdm_distance_yz(v, d_dist, 1, stream);
+    return complete(v, d_dist, 1, stream);
 }
 
 pdm_status pdm_plain_cached_distance_x(const pdm_volume* v, const void* d_bmin, const void* d_bmax,
@@ -627,7 +628,7 @@ pdm_status pdm_full_recompute_cached(const pdm_volume* v, const void* d_bmin, co
                                      const float* h_alpha, uint8_t* d_dist, hipStream_t stream) {
     pdm_status st = pdm_plain_cached_distance_x(v, d_bmin, d_bmax, h_alpha, d_dist, stream);
     if (st != PDM_OK) return st;
-    return pdm_distance_yz(v, d_dist, 1, stream);
+    return complete(v, d_dist, 1, stream);
 }
 
 pdm_status pdm_pom_exact_distance_x(const pdm_volume* v, const void* d_volume,
@@ -684,7 +685,7 @@ pdm_status pdm_full_recompute_exact(const pdm_volume* v, const void* d_volume,
                                     const float* h_alpha, uint8_t* d_dist, hipStream_t stream) {
     pdm_status st = pdm_plain_exact_distance_x(v, d_volume, h_alpha, d_dist, stream);
     if (st != PDM_OK) return st;
-    return pdm_distance_yz(v, d_dist, 1, stream);
+    return complete(v, d_dist, 1, stream);
 }
 
 const char* pdm_status_string(pdm_status s) {

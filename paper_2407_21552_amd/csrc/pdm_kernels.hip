@@ -2681,10 +2681,16 @@ static hipError_t launch_axis(uint8_t* maps, int count, int Bx, int By, int Bz, 
     return hipGetLastError();
 }
 
-hipError_t launch_distance_yz(uint8_t* maps, int count, int Bx, int By, int Bz, hipStream_t s) {
+hipError_t launch_distance_yz(uint8_t* maps, int count, int Bx, int By, int Bz, bool x_distances,
+                              hipStream_t s) {
     for (int axis = 1; axis <= 2; ++axis) {
         const int m = axis == 1 ? By : Bz;
         if (m == 1) continue;  // a line of one brick is unchanged
+        if (axis == 1 && x_distances && slice_y_fits(Bx, By)) {
+            const hipError_t e = launch_slice_y(maps, count, Bx, By, Bz, s);
+            if (e != hipSuccess) return e;
+            continue;
+        }
         const hipError_t e = launch_axis(maps, count, Bx, By, Bz, axis, s);
         if (e != hipSuccess) return e;
     }

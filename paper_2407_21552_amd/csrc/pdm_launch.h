@@ -184,13 +184,19 @@ hipError_t launch_copy_word(const uint32_t* src, uint32_t* dst, hipStream_t s);
 // bytes) by raster sweeps; the caller asks sweep_fits first.
 bool sweep_fits(int count, int Bx, int By, int Bz);
 hipError_t launch_sweep(uint8_t* maps, int count, int Bx, int By, int Bz, hipStream_t s);
+// The y pass over x distances, slice by slice (slice_y_fits first).
+bool slice_y_fits(int Bx, int By);
+hipError_t launch_slice_y(uint8_t* maps, int count, int Bx, int By, int Bz, hipStream_t s);
 // The same for the y and z phases of a batched build: whether the batch takes
 // the sweeps, the volumes' work-groups (items of the y and z phases zeroed),
 // and the launches, after the rows phase.
 bool batch_sweep_fits(const BatchVol* vols, int count);
 void batch_sweep_items(BatchVol* vols, int count);
 hipError_t launch_batch_sweep(const BatchVol* h_vols, int count, const BatchVol* d_vols, hipStream_t s);
-hipError_t launch_distance_yz(uint8_t* maps, int count, int Bx, int By, int Bz, hipStream_t s);
+// The y and z passes by line scans: on any bytes, or, with x_distances, on this
+// library's own x distances (the y pass may then take the slices).
+hipError_t launch_distance_yz(uint8_t* maps, int count, int Bx, int By, int Bz, bool x_distances,
+                              hipStream_t s);
 // out = element-wise min of the listed maps of G bytes (255 for none); any
 // size and pointer alignment.
 hipError_t launch_combine(const MapList& maps, int64_t G, uint8_t* out, hipStream_t s);

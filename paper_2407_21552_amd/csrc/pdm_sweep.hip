@@ -315,6 +315,113 @@ __global__ void __launch_bounds__(64 * kSweepBatchWaves) k_batch_sweep(const Bat
         sweep<PH, false, true, true>(t, lds);
 }
 
+// ---------------------------------------------------------------------------
+// k_slice_y: the y pass over slices (rows of x distances), in place, two waves
+// to a slice (64/W slices side by side in the lanes), each with its half of
+// the rows in registers: each sweeps its half from the outside in, the waves
+// exchange the row that the next one would build on, and each sweeps back
+// from the inside out over its own results.  A one-sided sweep over the other
+// direction's results, started from the other half's last row, is the
+// two-sided pass.  No table, no LDS but for the exchange, and a slice is a
+// work-group of its own: enough of them for one map already.
+//
+// NCH: chunks of 16 rows a wave's half spans.  A half of fewer rows starts with
+// rows outside the grid, at the cap: they change nothing.
+// Bound by the waves' chain of 2 x By/2 rows (13 vector instructions each) for
+// one map, by memory for many.  Measured against the line scans: 32 maps of
+// 128x128x115 57 -> 21 us (5.7 TB/s read and written), one map of 256x256x199
+// 24 -> 13 us, of 128x122x113 11 -> 7 us.
+// ---------------------------------------------------------------------------
+template <int NCH, bool GENERAL>
+__global__ void __launch_bounds__(2 * kWave) k_slice_y(uint8_t* __restrict__ maps, int64_t slices, int Bx,
+                                                       int By, int W) {
+    constexpr int NR = 16 * NCH;
+    __shared__ RowQuad inner[2][kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int half = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int per = kWave / W, seg = lane / W, q = lane & (W - 1);
+    const int64_t s0 = (int64_t)blockIdx.x * per;
+    const int here = (int)(slices - s0 < per ? slices - s0 : per);
+    const int plane = Bx * By;
+    const int nb = seg < here ? max(0, min(4, Bx - 4 * q)) : 0;
+    const uint32_t pad = GENERAL && nb < 4 ? ~0u << (8 * nb) : 0u;
+    const uint32_t edge_l = q == 0 ? kBeyond : 0u, edge_r = q == W - 1 ? kBeyond : 0u;
+    const bool cut = GENERAL && nb > 0 && nb < 4;  // the row's last 4 bytes, shifted
+    const int shift = cut ? 8 * (4 - nb) : 0;
+    const int voff = nb > 0 ? seg * plane + 4 * q - shift / 8 : -4;
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(maps + s0 * plane, (short)0, here * plane, kBufferRaw);
+    const int rows = half == 0 ? By / 2 : By - By / 2;
+    const int out = NR - rows;  // rows outside the grid, first
+    const int ystep = half == 0 ? Bx : -Bx;
+    int off = half == 0 ? 0 : (By - 1) * Bx;
+    uint32_t w[NR], all = ~0u;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        w[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, voff, off, 0);
+        off += i < 16 && i < out ? 0 : ystep;
+    }
+    const RowQuad cap = {kCap2, kCap2};
+    RowQuad X = cap;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        uint32_t h = w[i];
+        if (GENERAL) h = (h >> shift) | pad;
+        if (i < 16) h |= i < out ? ~0u : 0u;
+        all &= h;
+        w[i] = sweep_row(even_bytes(h), odd_bytes(h), cap, X, edge_l, edge_r);
+    }
+    inner[half][lane] = X;
+    __syncthreads();
+    X = inner[1 - half][lane];
+    // no brick in the slices: everything stays at the cap
+    if (__ballot(all != ~0u || pk_min16(pk_min16(X.e, X.o), kCap2) != kCap2) == 0ull) return;
+    __asm__("" : "+s"(off));  // one running offset, not a register for each row's
+#pragma unroll
+    for (int i = NR - 1; i >= 0; --i) {
+        uint32_t v = sweep_row(even_bytes(w[i]), odd_bytes(w[i]), cap, X, edge_l, edge_r);
+        if constexpr (GENERAL) {
+            const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xf, 0xf, true);
+            v = cut ? (uint32_t)((((uint64_t)v << 32) | prev) >> (32 - shift)) : v;
+        }
+        off -= ystep;
+        if (i >= 16 || i >= out) __builtin_amdgcn_raw_buffer_store_b32(v, rs, voff, off, 0);
+    }
+}
+
+static int row_lanes(int Bx) {
+    int W = 1;  // lanes per row: the power of two with 4W >= Bx
+    while (4 * W < Bx) W *= 2;
+    return W;
+}
+
+// Whether k_slice_y takes the y pass of these grids: whole quads of bricks in a
+// wave, rows in registers.  It is the faster one at every size measured, from
+// one map of 16x16x16 bricks (where both are a launch) up.
+bool slice_y_fits(int Bx, int By) { return Bx >= 4 && Bx <= 256 && By >= 2 && By <= 256; }
+
+hipError_t launch_slice_y(uint8_t* maps, int count, int Bx, int By, int Bz, hipStream_t s) {
+    const int W = row_lanes(Bx), per = kWave / W;
+    const int64_t slices = (int64_t)count * Bz, blocks = (slices + per - 1) / per;
+    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    const int nch = ((By + 1) / 2 + 15) / 16;
+    const bool general = 4 * W != Bx || slices % per != 0;
+    switch (nch) {
+#define PDM_SLICE_CASE(N)                                                                              \
+    case N:                                                                                            \
+        if (general)                                                                                   \
+            k_slice_y<N, true><<<(unsigned)blocks, 2 * kWave, 0, s>>>(maps, slices, Bx, By, W);        \
+        else                                                                                           \
+            k_slice_y<N, false><<<(unsigned)blocks, 2 * kWave, 0, s>>>(maps, slices, Bx, By, W);       \
+        break;
+        PDM_SLICE_CASE(1) PDM_SLICE_CASE(2) PDM_SLICE_CASE(3) PDM_SLICE_CASE(4)
+        PDM_SLICE_CASE(5) PDM_SLICE_CASE(6) PDM_SLICE_CASE(7) PDM_SLICE_CASE(8)
+#undef PDM_SLICE_CASE
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 // Steps of one sweep over np planes of By rows with NW waves.
 static int64_t sweep_steps(int np, int By, int NW) {
     const int nblk = (By + kSweepRows - 1) / kSweepRows;
@@ -334,12 +441,6 @@ static int sweep_waves(int np, int By) {
     for (int nw = 2; nw <= kSweepWaves; ++nw)
         if (sweep_steps(np, By, nw) < sweep_steps(np, By, best)) best = nw;
     return best;
-}
-
-static int row_lanes(int Bx) {
-    int W = 1;  // lanes per row: the power of two with 4W >= Bx
-    while (4 * W < Bx) W *= 2;
-    return W;
 }
 
 // Microseconds the line scans take per megabyte of maps, one pass over lines
