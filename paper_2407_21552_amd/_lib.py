@@ -624,7 +624,7 @@ def _batch_config(config):
 
 
 def batch_build(items, workspace, config=None, stream=None) -> None:
-    """Bricks and PDMs of several volumes in three grouped launches.
+    """Bricks and PDMs of several volumes in grouped launches.
     items: sequence of (desc, volume, bmin, bmax, bounds, pdms); workspace: a
     uint8 device tensor of batch_workspace_bytes(len(items)) bytes or more
     (it receives the descriptors; keep it until the stream has passed);

@@ -502,7 +502,8 @@ pdm_status batch_prepare(const pdm_batch_volume* h_vols, int32_t count, const pd
         d.row_groups = (g.by + d.rows - 1) / d.rows;
         d.items[0] = g.bz * d.row_groups;
         d.items[1] = g.by > 1 ? g.bz * d.chunks : 0;  // a pass over lines of 1 brick is the identity
-        d.items[2] = g.bz > 1 ? g.by * d.chunks : 0;
+        const int64_t columns = (int64_t)it.n * g.bx * g.by, pass = 64 * c.lines_mult;
+        d.items[2] = g.bz > 1 ? (int32_t)((columns + pass - 1) / pass) : 0;
         work[k] = (int64_t)it.n * g.count;
     }
     // order of the volumes' items (the same in every phase)
@@ -516,8 +517,17 @@ pdm_status batch_prepare(const pdm_batch_volume* h_vols, int32_t count, const pd
                 order[b - 1] = t;
             }
     for (int32_t k = 0; k < count; ++k) vols[k] = tmp[order[k]];
-    // grouped launches: the y and z phases by sweeps where those are faster
-    if (c.single_launch == 0 && pdm::batch_sweep_fits(vols, count)) pdm::batch_sweep_items(vols, count);
+    // grouped launches: the y and z phases by sweeps, or the y phase by slices
+    if (c.single_launch == 0) {
+        if (pdm::batch_sweep_fits(vols, count))
+            pdm::batch_sweep_items(vols, count);
+        else
+            for (int32_t k = 0; k < count; ++k)
+                if (pdm::slice_y_fits(vols[k].Bx, vols[k].By)) {
+                    vols[k].slices = 1;
+                    vols[k].items[1] = 0;
+                }
+    }
     totals[0] = totals[1] = totals[2] = 0;
     for (int ph = 0; ph < 3; ++ph)
         for (int32_t k = 0; k < count; ++k) {

@@ -85,16 +85,25 @@ struct BatchVol {
     int64_t G;
     int64_t first[3];  // first item of this volume in each phase (rows, y, z)
     int32_t items[3];  // items per phase
-    int32_t chunks;    // items per slice (y) or row (z): ceil(n*Bx / (64*lines_mult))
+    int32_t chunks;    // y items per slice: ceil(n*Bx / (64*lines_mult))
     int32_t nx, ny, nz, Bx, By, Bz, bytes, n, levels, store_vec;
     int32_t rows;        // brick rows per first-phase item
     int32_t row_groups;  // first-phase items per z slice: ceil(By / rows)
     int32_t row_lanes;   // lanes per brick row in the first phase (power of two)
     int32_t sweep_items[2];  // sweep work-groups, planes of many rows and of few (0: line scans)
     int32_t sweep_first[2];  // first of them within its launch
-    int32_t pad1[2];
+    int32_t slices;      // the y pass runs by slices: no scan items
+    int32_t pad1;
     int32_t bounds[257];
 };
+
+// First work-group of each volume in one launch (kernel argument; a lane a
+// volume).  Volumes without work-groups share the next one's first.
+struct BatchBlocks {
+    int32_t count;
+    int32_t first[64];
+};
+static_assert(PDM_BATCH_MAX_ITEMS <= 64, "one lane per volume");
 
 // Grid-barrier state of the single-launch batched build, one word per
 // 128-byte line, zeroed before each launch.
@@ -187,6 +196,8 @@ hipError_t launch_sweep(uint8_t* maps, int count, int Bx, int By, int Bz, hipStr
 // The y pass over x distances, slice by slice (slice_y_fits first).
 bool slice_y_fits(int Bx, int By);
 hipError_t launch_slice_y(uint8_t* maps, int count, int Bx, int By, int Bz, hipStream_t s);
+// The same for the volumes of a batch whose y pass has no scan items.
+hipError_t launch_batch_slice_y(const BatchVol* h_vols, int count, const BatchVol* d_vols, hipStream_t s);
 // The same for the y and z phases of a batched build: whether the batch takes
 // the sweeps, the volumes' work-groups (items of the y and z phases zeroed),
 // and the launches, after the rows phase.

@@ -333,14 +333,12 @@ __global__ void __launch_bounds__(64 * kSweepBatchWaves) k_batch_sweep(const Bat
 // 24 -> 13 us, of 128x122x113 11 -> 7 us.
 // ---------------------------------------------------------------------------
 template <int NCH, bool GENERAL>
-__global__ void __launch_bounds__(2 * kWave) k_slice_y(uint8_t* __restrict__ maps, int64_t slices, int Bx,
-                                                       int By, int W) {
+__device__ __forceinline__ void slice_y(uint8_t* maps, int64_t slices, int64_t s0, int Bx, int By, int W,
+                                        RowQuad (&inner)[2][kWave]) {
     constexpr int NR = 16 * NCH;
-    __shared__ RowQuad inner[2][kWave];
     const int lane = threadIdx.x & (kWave - 1);
     const int half = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int per = kWave / W, seg = lane / W, q = lane & (W - 1);
-    const int64_t s0 = (int64_t)blockIdx.x * per;
     const int here = (int)(slices - s0 < per ? slices - s0 : per);
     const int plane = Bx * By;
     const int nb = seg < here ? max(0, min(4, Bx - 4 * q)) : 0;
@@ -389,6 +387,37 @@ __global__ void __launch_bounds__(2 * kWave) k_slice_y(uint8_t* __restrict__ map
     }
 }
 
+template <int NCH, bool GENERAL>
+__global__ void __launch_bounds__(2 * kWave) k_slice_y(uint8_t* __restrict__ maps, int64_t slices, int Bx,
+                                                       int By, int W) {
+    __shared__ RowQuad inner[2][kWave];
+    slice_y<NCH, GENERAL>(maps, slices, (int64_t)blockIdx.x * (kWave / W), Bx, By, W, inner);
+}
+
+// The volumes of a batch with 16 * LO + 1 .. 16 * HI rows to a half.
+template <int LO, int HI>
+__global__ void __launch_bounds__(2 * kWave) k_batch_slice_y(const BatchVol* __restrict__ vols, BatchBlocks b) {
+    __shared__ RowQuad inner[2][kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    // the last volume whose first work-group is not after this one
+    const uint64_t before = __ballot(lane < b.count && b.first[lane] <= (int)blockIdx.x);
+    const int k = 63 - __clzll((long long)before);
+    const BatchVol& d = vols[k];
+    const int W = d.row_lanes, Bx = d.Bx, By = d.By;
+    const int64_t s0 = (int64_t)((int)blockIdx.x - b.first[k]) * (kWave / W), slices = (int64_t)d.n * d.Bz;
+    switch (((By + 1) / 2 + 15) / 16) {
+#define PDM_SLICE_CASE(N)                                                       \
+    case N:                                                                     \
+        if constexpr (N > LO && N <= HI)                                        \
+            slice_y<N, true>(d.pdms, slices, s0, Bx, By, W, inner);             \
+        break;
+        PDM_SLICE_CASE(1) PDM_SLICE_CASE(2) PDM_SLICE_CASE(3) PDM_SLICE_CASE(4)
+        PDM_SLICE_CASE(5) PDM_SLICE_CASE(6) PDM_SLICE_CASE(7) PDM_SLICE_CASE(8)
+#undef PDM_SLICE_CASE
+        default: break;
+    }
+}
+
 static int row_lanes(int Bx) {
     int W = 1;  // lanes per row: the power of two with 4W >= Bx
     while (4 * W < Bx) W *= 2;
@@ -422,6 +451,28 @@ hipError_t launch_slice_y(uint8_t* maps, int count, int Bx, int By, int Bz, hipS
     return hipGetLastError();
 }
 
+template <int LO, int HI>
+static hipError_t launch_batch_slices(const BatchVol* h_vols, int count, const BatchVol* d_vols, hipStream_t s) {
+    BatchBlocks b;
+    int64_t blocks = 0;
+    b.count = count;
+    for (int k = 0; k < count; ++k) {
+        const BatchVol& d = h_vols[k];
+        const int nch = ((d.By + 1) / 2 + 15) / 16, per = kWave / d.row_lanes;
+        b.first[k] = (int32_t)blocks;
+        if (d.slices && nch > LO && nch <= HI) blocks += ((int64_t)d.n * d.Bz + per - 1) / per;
+    }
+    if (blocks == 0) return hipSuccess;
+    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    k_batch_slice_y<LO, HI><<<(unsigned)blocks, 2 * kWave, 0, s>>>(d_vols, b);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_slice_y(const BatchVol* h_vols, int count, const BatchVol* d_vols, hipStream_t s) {
+    const hipError_t e = launch_batch_slices<0, 4>(h_vols, count, d_vols, s);
+    return e == hipSuccess ? launch_batch_slices<4, 8>(h_vols, count, d_vols, s) : e;
+}
+
 // Steps of one sweep over np planes of By rows with NW waves.
 static int64_t sweep_steps(int np, int By, int NW) {
     const int nblk = (By + kSweepRows - 1) / kSweepRows;
@@ -449,12 +500,13 @@ static int sweep_waves(int np, int By) {
 // the waves of a compute unit).
 static double scan_us_per_mb(int m) { return 0.45 + 0.0023 * m; }
 
-// Whether the sweeps take all maps of a grid.  They run one work-group per
-// group of 64/W maps and half of the planes, each a chain of steps of about
-// 0.95 us at 16 waves, so they win where there are many bytes for few steps:
-// 64 maps of 256x256x199 bricks 904 us against 1650 for the line scans, 256
-// maps of 96x96x96 196 against 285, but 64 maps of 160x128x128 280 against
-// 232, and 32 of 128x128x115 255 against 114.
+// Whether the sweeps take all maps of a grid, and not the slices (0.36 us per
+// megabyte) and the z scans.  They run one work-group per group of 64/W maps
+// and half of the planes, each a chain of steps of about 0.95 us at 16 waves,
+// so they win where there are many bytes for few steps: 64 maps of 256x256x199
+// bricks 901 us against 1217, 256 maps of 128x128x128 424 against 571; but 64
+// maps of 256x256x128 607 against 598, of 175x175x175 593 against 485, 256 of
+// 75x75x75 185 against 130.
 bool sweep_fits(int count, int Bx, int By, int Bz) {
     if (Bx < 4 || Bx > 256 || By > 256 || Bz < 2) return false;
     const int per = kWave / row_lanes(Bx);
@@ -465,36 +517,33 @@ bool sweep_fits(int count, int Bx, int By, int Bz) {
     const double rounds = std::max(1.0, (double)groups / 256.0);
     const double t_sweep = 2.0 * (0.95 * (double)sweep_steps(np, By, nw) * rounds + 8.0);
     const double mb = 1e-6 * (double)G * count;
-    return t_sweep < 0.9 * mb * (scan_us_per_mb(By) + scan_us_per_mb(Bz));
+    return t_sweep < mb * (0.36 + scan_us_per_mb(Bz));
 }
 
 static int batch_sweep_parts(int Bz) { return Bz >= kSweepMinPlanes ? 2 : 1; }
 
-// Whether the sweeps take the y and z phases of a batch: their time is that of
-// all rows (0.11 us per 1000 rows of a wave and sweep, measured on the batch
-// of 48 volumes of 96..640 voxels per axis) or of the longest chain of steps
-// (0.7 us each), that of the line scans their bytes (tables sized for the
-// longest line of the batch).  Measured: that batch 2640 -> 1640 us; 12
-// volumes of 60..400 voxels 35 us slower, so they keep the scans.
+// Whether the sweeps take the y and z phases of a batch, and not the slices and
+// the z scans: their time follows all rows and the longest chain of steps, that
+// of the others the bytes (fits of the measured batches, sweeps against slices
+// and scans: 4 volumes of 900..1024 voxels per axis 2645 us against 3780, 12 of
+// 400..1000 2340 against 3230; 48 of 96..640 1833 against 1780, 6 of 300..640
+// 571 against 319, 48 of 60..200 194 against 92).
 bool batch_sweep_fits(const BatchVol* vols, int count) {
-    double rows = 0.0, mb = 0.0;
+    double rows = 0.0, t_lines = 0.0;
     int64_t chain = 0;
-    int longest = 0;
     for (int k = 0; k < count; ++k) {
         const BatchVol& d = vols[k];
         const int per = kWave / d.row_lanes, parts = batch_sweep_parts(d.Bz);
         rows += (double)((d.n + per - 1) / per) * d.By * d.Bz;
-        mb += 1e-6 * (double)d.G * d.n;
         chain = std::max(chain, sweep_steps((d.Bz + parts - 1) / parts, d.By, kSweepBatchWaves));
-        longest = std::max(longest, std::max(d.By, d.Bz));
+        t_lines += 1e-6 * (double)d.G * d.n * (0.46 + 1.3 * scan_us_per_mb(d.Bz));
     }
-    const double t_sweep = 2.0 * std::max(0.11e-3 * rows, 0.7 * (double)chain) + 16.0;
-    return t_sweep < 0.9 * 1.28 * 2.0 * mb * scan_us_per_mb(longest);
+    return 0.2e-3 * rows + 0.84 * (double)chain + 30.0 < t_lines;
 }
 
 // Sweep work-groups of the volumes that take them, planes of more than 104
 // rows apart from the others (their rings leave fewer work-groups to a compute
-// unit); volumes narrower than a quad keep the line scans.
+// unit); volumes narrower than a quad keep the line scans in both phases.
 void batch_sweep_items(BatchVol* vols, int count) {
     int32_t first[2] = {0, 0};
     for (int k = 0; k < count; ++k) {

@@ -1,7 +1,9 @@
 """The y pass over slices (two waves to a slice, rows in registers) against the
 line scans: a plain recompute equals its x pass followed by pdm_distance_yz,
 which always runs the scans, and so does a build too small for the sweeps, at
-row counts on either side of every chunk and at row widths of every lane count."""
+row counts on either side of every chunk and at row widths of every lane count.
+Then the builds on the sweeps' side of the rule, at grids that reach every
+variant of the sweep kernel, and batches on either side of it."""
 import numpy as np
 import pytest
 
@@ -52,3 +54,56 @@ def test_row_counts(by, voxels):
 def test_row_widths(bx, voxels):
     for by in (30, 131):
         _check(bx, by, 17, voxels)
+
+
+# (nz, ny, nx), partitions, all where the sweeps are the faster ones: whole
+# quads and lanes; padded lanes; an odd map count; rows that end inside a quad
+@pytest.mark.parametrize("shape,n", [((512, 512, 512), 256), ((512, 512, 496), 256), ((512, 504, 512), 255),
+                                     ((500, 509, 506), 254), ((795, 1010, 1024), 64)])
+@pytest.mark.parametrize("voxels", [60, 20000])
+def test_sweep_side(shape, n, voxels):
+    import paper_2407_21552_amd as pdm
+    g = torch.Generator(device="cuda").manual_seed(n + voxels)
+    vol = torch.zeros(shape, dtype=torch.uint8, device="cuda")
+    at = torch.randint(0, vol.numel(), (voxels,), generator=g, device="cuda")
+    vol.view(-1)[at] = torch.randint(0, 256, (voxels,), generator=g, device="cuda").to(torch.uint8)
+    bounds = np.array([(p * 256) // n for p in range(n + 1)], np.int32)
+    v = pdm.Volume(vol, 256, bounds)
+    v.build()
+    want = torch.empty_like(v.pdms)
+    pdm.pom_distance_x(v.desc, v.bmin, v.bmax, bounds, want)
+    pdm.distance_yz(v.desc, want, n)
+    assert torch.equal(v.pdms, want)
+
+
+# large volumes (sweeps); mixed ones (slices, scans of every class of lengths,
+# rows narrower than a quad, single rows and planes)
+@pytest.mark.parametrize("shapes,n", [([(800, 1000, 1010), (900, 1024, 1024), (60, 700, 9), (7, 1, 640)], 64),
+                                      ([(90, 70, 66), (300, 421, 130), (500, 60, 257), (1020, 40, 33),
+                                        (64, 1024, 5), (1, 300, 300), (200, 1, 90), (3, 2, 1), (70, 90, 15)], 37)])
+def test_batch_sides(shapes, n):
+    import paper_2407_21552_amd as pdm
+    items, want = [], []
+    for k, s in enumerate(shapes):
+        g = torch.Generator(device="cuda").manual_seed(k)
+        vol = torch.zeros(s, dtype=torch.uint8, device="cuda")
+        at = torch.randint(0, vol.numel(), (400,), generator=g, device="cuda")
+        vol.view(-1)[at] = torch.randint(0, 256, (400,), generator=g, device="cuda").to(torch.uint8)
+        bounds = np.array([(p * 256) // n for p in range(n + 1)], np.int32)
+        v = pdm.Volume(vol, 256, bounds)
+        pdms = torch.empty_like(v.pdms)
+        v.bmin.fill_(3)
+        v.bmax.fill_(3)
+        pdm.build_bricks(v.desc, vol, v.bmin, v.bmax)
+        pdm.pom_distance_x(v.desc, v.bmin, v.bmax, bounds, pdms)
+        pdm.distance_yz(v.desc, pdms, n)
+        want.append(pdms)
+        v.pdms.fill_(7)
+        items.append((v.desc, v.volume, v.bmin, v.bmax, v.bounds, v.pdms))
+    for cfg in (None, {"single_launch": 1, "lines_mult": 3}):
+        ws = torch.zeros(pdm.batch_workspace_bytes(len(items)), dtype=torch.uint8, device="cuda")
+        pdm.batch_build(items, ws, cfg)
+        torch.cuda.synchronize()
+        for it, w in zip(items, want):
+            assert torch.equal(it[5], w)
+            it[5].fill_(7)
