@@ -70,6 +70,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBPS = 8000.0  # MI355X HBM3E
 KERNEL_SRC = os.path.join(ROOT, "paper_2407_21552_amd", "csrc", "pdm_kernels.hip")
+MORE_KERNEL_SRC = [os.path.join(ROOT, "paper_2407_21552_amd", "csrc", f) for f in ("pdm_sweep.hip", "pdm_packed.h")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_tube_tree_1024x1024x795.md")
 
 # paper's numbers (RTX 4090, OpenGL), kingsnake 1024x1024x795, 64 partitions
@@ -87,11 +88,11 @@ def log(*a):
 
 
 def kernel_hash() -> str:
-    """Hash of the kernel source with comments and whitespace removed, so a
+    """Hash of the kernel sources with comments and whitespace removed, so a
     comment edit does not orphan the counter record while any code change
     does."""
     import re
-    text = open(KERNEL_SRC).read()
+    text = "\n".join(open(f).read() for f in [KERNEL_SRC] + MORE_KERNEL_SRC)
     text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
     text = re.sub(r"//[^\n]*", " ", text)
     text = " ".join(text.split())

@@ -28,6 +28,8 @@
 //                   or offsets past 31 bits).
 //   k_dist_axis, k_dist_split  the same pass with lines staged in LDS (lines
 //                   of at most 16 bricks).
+//   k_sweep, k_batch_sweep, k_slice_y, k_batch_slice_y  (pdm_sweep.hip) the y
+//                   and z passes over x distances, rows of bricks at a time.
 //   k_combine       min over a list of G-byte maps (the active PDMs, or the
 //                   range-table maps covering them), 16 bytes per lane.
 //   k_range_level   one level of the range table: min of two maps.
@@ -35,7 +37,8 @@
 //   k_batch_combine_maps  the same through range tables (a map list each).
 //   k_batch_rows, k_batch_scan, k_batch_single
 //                   batched build of up to 48 volumes: grouped launches per
-//                   phase, or one cooperative launch with grid barriers.
+//                   phase (with the slices or sweeps of pdm_sweep.hip), or one
+//                   cooperative launch with grid barriers.
 //   k_pom_exact_x   EXACT reading: per-brick partition masks from the voxels,
 //                   then the x distances of every partition.
 //   k_plain_exact_x EXACT reading of the plain method's occupancy.
@@ -50,6 +53,7 @@
 
 namespace pdm {
 
+constexpr int kWave = 64;
 constexpr int kSegBricks = 4 * kWave;  // bricks of one x segment handled by a wave
 constexpr int kNone = 1 << 20;         // "no occupied brick": farther than any cap
 

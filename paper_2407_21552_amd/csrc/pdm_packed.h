@@ -5,7 +5,6 @@
 
 namespace pdm {
 
-constexpr int kWave = 64;
 
 typedef unsigned short us2 __attribute__((ext_vector_type(2)));
 
