@@ -107,3 +107,26 @@ def test_batch_sides(shapes, n):
         for it, w in zip(items, want):
             assert torch.equal(it[5], w)
             it[5].fill_(7)
+
+
+@pytest.mark.parametrize("off", [1, 2, 3])
+@pytest.mark.parametrize("bx,by,bz,n", [(32, 40, 9, 3), (37, 33, 5, 3), (128, 128, 127, 256)])
+def test_any_alignment(off, bx, by, bz, n):
+    """Maps at any byte address, slices and sweeps; bytes around them stay."""
+    import paper_2407_21552_amd as pdm
+    vol = _volume(bx, by, bz, 500)
+    bounds = np.array([(p * 256) // n for p in range(n + 1)], np.int32)
+    v = pdm.Volume(vol, 256, bounds)
+    v.build()
+    G = v.dist.numel()
+    buf = torch.full((n * G + 8,), 77, dtype=torch.uint8, device="cuda")
+    pdm.build_partitions(v.desc, v.bmin, v.bmax, bounds, buf[off:off + n * G])
+    assert torch.equal(buf[off:off + n * G], v.pdms.reshape(-1))
+    assert (buf[:off] == 77).all() and (buf[off + n * G:] == 77).all()
+    alpha = np.zeros(256, np.float32)
+    alpha[120:] = 1.0
+    v.full_recompute(alpha)
+    buf.fill_(77)
+    pdm.full_recompute(v.desc, vol, alpha, buf[off:off + G])
+    assert torch.equal(buf[off:off + G], v.dist.reshape(-1))
+    assert (buf[:off] == 77).all() and (buf[off + G:] == 77).all()
