@@ -2412,7 +2412,7 @@ __global__ void __launch_bounds__(kWave) k_batch_single(const BatchVol* __restri
 // the same stream.  Only the bounds a volume has travel (a descriptor has room
 // for 257), and the state is cleared by the first launch: a launch costs more
 // than what it moves.  48 volumes of 16 .. 64 partitions take 5 launches, and
-// took 18 with whole descriptors and a launch to clear (4.4 us each in a row):
+// took 18 with whole descriptors and a launch to clear (4.4 us each in a row; the 5 take 5.4):
 // that build 3218 -> 3200 us, of 48 volumes of 30..64 voxels 333 -> 315.
 struct UploadChunk {
     int32_t from, pieces;  // this launch's run of the batch's pieces
