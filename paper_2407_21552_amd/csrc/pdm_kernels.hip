@@ -2787,6 +2787,24 @@ hipError_t launch_batch_maps(BatchMapsArgs& a, hipStream_t s) {
 constexpr int kScanClasses = 5;
 constexpr int kScanClass[kScanClasses] = {0, 64, 104, 160, kMaxLine};
 
+// Work-groups of a kernel that are resident on a compute unit at once.  The
+// runtime's figure divides the unit's LDS by the bytes asked for, but LDS is
+// handed out in pieces of 1280 bytes: with 15,376 bytes it says 10 and 9 are
+// (as counted by a kernel that records when its work-groups start), and a
+// barrier over 10 a unit would never be complete.
+static hipError_t resident_groups(const void* kernel, int threads, size_t dynamic_lds, int dev, int* out) {
+    constexpr size_t kLdsPiece = 1280;
+    hipFuncAttributes attr;
+    int lds_unit = 0;
+    hipError_t e = hipFuncGetAttributes(&attr, kernel);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&lds_unit, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev);
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(out, kernel, threads, dynamic_lds);
+    if (e != hipSuccess) return e;
+    const size_t lds = (attr.sharedSizeBytes + dynamic_lds + kLdsPiece - 1) / kLdsPiece * kLdsPiece;
+    if (lds > 0) *out = min(*out, (int)((size_t)lds_unit / lds));
+    return hipSuccess;
+}
+
 hipError_t launch_batch_build(const BatchVol* h_vols, int count, BatchVol* d_vols,
                               BatchSync* d_sync, const int64_t totals[3], int lines_mult,
                               int single, hipStream_t s) {
@@ -2821,8 +2839,7 @@ hipError_t launch_batch_build(const BatchVol* h_vols, int count, BatchVol* d_vol
         int dev = 0, cus = 0, per_cu = 0;
         hipError_t e = hipGetDevice(&dev);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e == hipSuccess)
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch_single, kWave, lds);
+        if (e == hipSuccess) e = resident_groups(reinterpret_cast<const void*>(k_batch_single), kWave, lds, dev, &per_cu);
         if (e != hipSuccess) return e;
         const int64_t grid = (int64_t)per_cu * cus;
         if (grid < 1 || grid > INT32_MAX) return hipErrorInvalidConfiguration;
