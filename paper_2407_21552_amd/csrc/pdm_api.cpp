@@ -519,7 +519,9 @@ pdm_status batch_prepare(const pdm_batch_volume* h_vols, int32_t count, const pd
     for (int32_t k = 0; k < count; ++k) vols[k] = tmp[order[k]];
     // grouped launches: the y and z phases by sweeps, or the y phase by slices
     if (c.single_launch == 0) {
-        if (pdm::batch_sweep_fits(vols, count))
+        pdm::RouteGrid grids[PDM_BATCH_MAX];
+        for (int32_t k = 0; k < count; ++k) grids[k] = {vols[k].n, vols[k].Bx, vols[k].By, vols[k].Bz};
+        if (pdm::batch_sweep_fits(grids, count))
             pdm::batch_sweep_items(vols, count);
         else
             for (int32_t k = 0; k < count; ++k)

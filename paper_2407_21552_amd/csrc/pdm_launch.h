@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "pdm_route.h"
+
 #define PDM_PLAIN_MAX_SEGS 64    // x segments of 256 bricks: Bx <= 16384
 #define PDM_ALPHA_WORDS 512      // non-zero opacity bitmap: levels <= 16384
 #define PDM_EXACT_MAX_LEVELS 16384  // intensity -> partition table of the EXACT build
@@ -191,17 +193,14 @@ hipError_t batch_scratch(int dev, uint8_t** ptr, size_t* bytes);
 hipError_t launch_copy_word(const uint32_t* src, uint32_t* dst, hipStream_t s);
 // Completes `count` grids of x distances (rows of distances along x, not any
 // bytes) by raster sweeps; the caller asks sweep_fits first.
-bool sweep_fits(int count, int Bx, int By, int Bz);
 hipError_t launch_sweep(uint8_t* maps, int count, int Bx, int By, int Bz, hipStream_t s);
 // The y pass over x distances, slice by slice (slice_y_fits first).
-bool slice_y_fits(int Bx, int By);
 hipError_t launch_slice_y(uint8_t* maps, int count, int Bx, int By, int Bz, hipStream_t s);
 // The same for the volumes of a batch whose y pass has no scan items.
 hipError_t launch_batch_slice_y(const BatchVol* h_vols, int count, const BatchVol* d_vols, hipStream_t s);
-// The same for the y and z phases of a batched build: whether the batch takes
-// the sweeps, the volumes' work-groups (items of the y and z phases zeroed),
-// and the launches, after the rows phase.
-bool batch_sweep_fits(const BatchVol* vols, int count);
+// The same for the y and z phases of a batched build (batch_sweep_fits first):
+// the volumes' work-groups (items of the y and z phases zeroed), and the
+// launches, after the rows phase.
 void batch_sweep_items(BatchVol* vols, int count);
 hipError_t launch_batch_sweep(const BatchVol* h_vols, int count, const BatchVol* d_vols, hipStream_t s);
 // The y and z passes by line scans: on any bytes, or, with x_distances, on this

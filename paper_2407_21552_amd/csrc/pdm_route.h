@@ -1,0 +1,106 @@
+// pdm_route.h -- which kernels take the y and z passes of a build or recompute,
+// and the launch shapes that the choice is made on.  Host code without HIP, so
+// that it can be compiled and tested on its own.
+#pragma once
+#include <stdint.h>
+
+#include <algorithm>
+
+namespace pdm {
+
+constexpr int kWave = 64;
+// Rows per step of a wave (between two barriers).  8 measured within 3% for
+// 256-row planes and 7% slower for 96 (fewer blocks than the lag of 16 waves
+// needs).
+constexpr int kSweepRows = 4;
+constexpr int kSweepWaves = 16;       // most waves of a work-group
+constexpr int kSweepBatchWaves = 8;   // waves of a batch's work-groups
+constexpr int kSweepMinPlanes = 16;   // fewer planes are not cut in two parts in a batch
+
+// The maps of one volume: n grids of Bx x By x Bz bricks.
+struct RouteGrid {
+    int n, Bx, By, Bz;
+};
+
+// Lanes per row, 4 bricks each: the power of two with 4W >= Bx.
+inline int row_lanes(int Bx) {
+    int W = 1;
+    while (4 * W < Bx) W *= 2;
+    return W;
+}
+
+// Whether k_slice_y takes the y pass of these grids: whole quads of bricks in a
+// wave, rows in registers.  It is the faster one at every size measured, from
+// one map of 16x16x16 bricks (where both are a launch) up.
+inline bool slice_y_fits(int Bx, int By) { return Bx >= 4 && Bx <= 256 && By >= 2 && By <= 256; }
+
+// Steps of one sweep over np planes of By rows with NW waves.
+inline int64_t sweep_steps(int np, int By, int NW) {
+    const int nblk = (By + kSweepRows - 1) / kSweepRows;
+    const int period = std::max(nblk, 2 * NW);
+    return (int64_t)((np + NW - 1) / NW - 1) * period + nblk + 2 * (NW - 1);
+}
+
+// Waves of a work-group: the fewest steps.
+inline int sweep_waves(int np, int By) {
+    int best = 1;
+    for (int nw = 2; nw <= kSweepWaves; ++nw)
+        if (sweep_steps(np, By, nw) < sweep_steps(np, By, best)) best = nw;
+    return best;
+}
+
+// Microseconds the line scans take per megabyte of maps, one pass over lines
+// of m bricks (fits of measured passes: 0.67 at 96 bricks, 0.74 at 128, 0.91
+// at 199, 1.04 at 256: the longer the line, the larger its table and the fewer
+// the waves of a compute unit).
+inline double scan_us_per_mb(int m) { return 0.45 + 0.0023 * m; }
+
+// Whether the sweeps take all maps of a grid, and not the slices (0.36 us per
+// megabyte) and the z scans.  They run one work-group per group of 64/W maps
+// and half of the planes, each a chain of steps of about 0.95 us at 16 waves,
+// so they win where there are many bytes for few steps: 64 maps of 256x256x199
+// bricks 901 us against 1217, 256 maps of 128x128x128 424 against 571; but 64
+// maps of 256x256x128 607 against 598, of 175x175x175 593 against 485, 256 of
+// 75x75x75 185 against 130.
+inline bool sweep_fits(int count, int Bx, int By, int Bz) {
+    if (Bx < 4 || Bx > 256 || By > 256 || Bz < 2) return false;
+    const int per = kWave / row_lanes(Bx);
+    const int64_t G = (int64_t)Bx * By * Bz;
+    if (G * std::min(per, count) > INT32_MAX) return false;  // 32-bit offsets within a group
+    const int np = (Bz + 1) / 2 + 1, nw = sweep_waves(np, By);
+    const int64_t groups = 2 * (int64_t)((count + per - 1) / per);
+    const double rounds = std::max(1.0, (double)groups / 256.0);
+    const double t_sweep = 2.0 * (0.95 * (double)sweep_steps(np, By, nw) * rounds + 8.0);
+    const double mb = 1e-6 * (double)G * count;
+    return t_sweep < mb * (0.36 + scan_us_per_mb(Bz));
+}
+
+inline int batch_sweep_parts(int Bz) { return Bz >= kSweepMinPlanes ? 2 : 1; }
+
+// Launch a volume's sweeps are in: planes of more than 104 rows (0) apart from
+// the others (1).  A launch's rings are sized for its highest plane, 2 KB per 4
+// rows: up to 104 rows (52 KB) three work-groups share a compute unit's LDS.
+inline int batch_sweep_class(int By) { return By > 104 ? 0 : 1; }
+
+// Whether a volume's y and z passes are sweeps in a batch that takes them.
+inline bool batch_volume_sweeps(const RouteGrid& g) { return g.Bx >= 4; }
+
+// Whether the sweeps take the y and z phases of a batch, and not the slices and
+// the z scans: their time follows all rows and the longest chain of steps, that
+// of the others the bytes (fits of the measured batches, sweeps against slices
+// and scans: 4 volumes of 900..1024 voxels per axis 2645 us against 3780, 12 of
+// 400..1000 2340 against 3230; 48 of 96..640 1833 against 1780, 6 of 300..640
+// 571 against 319, 48 of 60..200 194 against 92).
+inline bool batch_sweep_fits(const RouteGrid* g, int count) {
+    double rows = 0.0, t_lines = 0.0;
+    int64_t chain = 0;
+    for (int k = 0; k < count; ++k) {
+        const int per = kWave / row_lanes(g[k].Bx), parts = batch_sweep_parts(g[k].Bz);
+        rows += (double)((g[k].n + per - 1) / per) * g[k].By * g[k].Bz;
+        chain = std::max(chain, sweep_steps((g[k].Bz + parts - 1) / parts, g[k].By, kSweepBatchWaves));
+        t_lines += 1e-6 * (double)g[k].Bx * g[k].By * g[k].Bz * g[k].n * (0.46 + 1.3 * scan_us_per_mb(g[k].Bz));
+    }
+    return 0.2e-3 * rows + 0.84 * (double)chain + 30.0 < t_lines;
+}
+
+}  // namespace pdm

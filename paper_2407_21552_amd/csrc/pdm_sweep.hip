@@ -45,14 +45,6 @@
 
 namespace pdm {
 
-constexpr int kWave = 64;
-// Rows per step of a wave (between two barriers).  8 measured within 3% for
-// 256-row planes and 7% slower for 96 (fewer blocks than the lag of 16 waves
-// needs).
-constexpr int kSweepRows = 4;
-constexpr int kSweepWaves = 16;            // most waves of a work-group
-constexpr int kSweepBatchWaves = 8;        // waves of a batch's work-groups
-constexpr int kSweepMinPlanes = 16;        // fewer planes are not cut in two parts in a batch
 constexpr int kBufferRaw = 0x00020000;     // raw buffer, 32-bit data format (gfx9 family)
 constexpr uint32_t kBeyond = 0x01FF01FFu;  // a neighbour outside the row: above every distance
 constexpr uint32_t kCap2 = 0x00FF00FFu;    // two capped distances
@@ -419,17 +411,6 @@ __global__ void __launch_bounds__(2 * kWave) k_batch_slice_y(const BatchVol* __r
     }
 }
 
-static int row_lanes(int Bx) {
-    int W = 1;  // lanes per row: the power of two with 4W >= Bx
-    while (4 * W < Bx) W *= 2;
-    return W;
-}
-
-// Whether k_slice_y takes the y pass of these grids: whole quads of bricks in a
-// wave, rows in registers.  It is the faster one at every size measured, from
-// one map of 16x16x16 bricks (where both are a launch) up.
-bool slice_y_fits(int Bx, int By) { return Bx >= 4 && Bx <= 256 && By >= 2 && By <= 256; }
-
 hipError_t launch_slice_y(uint8_t* maps, int count, int Bx, int By, int Bz, hipStream_t s) {
     const int W = row_lanes(Bx), per = kWave / W;
     const int64_t slices = (int64_t)count * Bz, blocks = (slices + per - 1) / per;
@@ -474,85 +455,21 @@ hipError_t launch_batch_slice_y(const BatchVol* h_vols, int count, const BatchVo
     return e == hipSuccess ? launch_batch_slices<4, 8>(h_vols, count, d_vols, s) : e;
 }
 
-// Steps of one sweep over np planes of By rows with NW waves.
-static int64_t sweep_steps(int np, int By, int NW) {
-    const int nblk = (By + kSweepRows - 1) / kSweepRows;
-    const int period = std::max(nblk, 2 * NW);
-    return (int64_t)((np + NW - 1) / NW - 1) * period + nblk + 2 * (NW - 1);
-}
-
 // LDS of a work-group: the rings hold one period of blocks in all.
 static size_t sweep_lds(int By, int NW) {
     const int nblk = (By + kSweepRows - 1) / kSweepRows;
     return (size_t)std::max(nblk, 2 * NW) * kSweepRows * kWave * sizeof(RowQuad);
 }
 
-// Waves of a work-group: the fewest steps.
-static int sweep_waves(int np, int By) {
-    int best = 1;
-    for (int nw = 2; nw <= kSweepWaves; ++nw)
-        if (sweep_steps(np, By, nw) < sweep_steps(np, By, best)) best = nw;
-    return best;
-}
-
-// Microseconds the line scans take per megabyte of maps, one pass over lines
-// of m bricks (fits of measured passes: 0.67 at 96 bricks, 0.74 at 128, 0.91
-// at 199, 1.04 at 256: the longer the line, the larger its table and the fewer
-// the waves of a compute unit).
-static double scan_us_per_mb(int m) { return 0.45 + 0.0023 * m; }
-
-// Whether the sweeps take all maps of a grid, and not the slices (0.36 us per
-// megabyte) and the z scans.  They run one work-group per group of 64/W maps
-// and half of the planes, each a chain of steps of about 0.95 us at 16 waves,
-// so they win where there are many bytes for few steps: 64 maps of 256x256x199
-// bricks 901 us against 1217, 256 maps of 128x128x128 424 against 571; but 64
-// maps of 256x256x128 607 against 598, of 175x175x175 593 against 485, 256 of
-// 75x75x75 185 against 130.
-bool sweep_fits(int count, int Bx, int By, int Bz) {
-    if (Bx < 4 || Bx > 256 || By > 256 || Bz < 2) return false;
-    const int per = kWave / row_lanes(Bx);
-    const int64_t G = (int64_t)Bx * By * Bz;
-    if (G * std::min(per, count) > INT32_MAX) return false;  // 32-bit offsets within a group
-    const int np = (Bz + 1) / 2 + 1, nw = sweep_waves(np, By);
-    const int64_t groups = 2 * (int64_t)((count + per - 1) / per);
-    const double rounds = std::max(1.0, (double)groups / 256.0);
-    const double t_sweep = 2.0 * (0.95 * (double)sweep_steps(np, By, nw) * rounds + 8.0);
-    const double mb = 1e-6 * (double)G * count;
-    return t_sweep < mb * (0.36 + scan_us_per_mb(Bz));
-}
-
-static int batch_sweep_parts(int Bz) { return Bz >= kSweepMinPlanes ? 2 : 1; }
-
-// Whether the sweeps take the y and z phases of a batch, and not the slices and
-// the z scans: their time follows all rows and the longest chain of steps, that
-// of the others the bytes (fits of the measured batches, sweeps against slices
-// and scans: 4 volumes of 900..1024 voxels per axis 2645 us against 3780, 12 of
-// 400..1000 2340 against 3230; 48 of 96..640 1833 against 1780, 6 of 300..640
-// 571 against 319, 48 of 60..200 194 against 92).
-bool batch_sweep_fits(const BatchVol* vols, int count) {
-    double rows = 0.0, t_lines = 0.0;
-    int64_t chain = 0;
-    for (int k = 0; k < count; ++k) {
-        const BatchVol& d = vols[k];
-        const int per = kWave / d.row_lanes, parts = batch_sweep_parts(d.Bz);
-        rows += (double)((d.n + per - 1) / per) * d.By * d.Bz;
-        chain = std::max(chain, sweep_steps((d.Bz + parts - 1) / parts, d.By, kSweepBatchWaves));
-        t_lines += 1e-6 * (double)d.G * d.n * (0.46 + 1.3 * scan_us_per_mb(d.Bz));
-    }
-    return 0.2e-3 * rows + 0.84 * (double)chain + 30.0 < t_lines;
-}
-
-// Sweep work-groups of the volumes that take them, planes of more than 104
-// rows apart from the others (their rings leave fewer work-groups to a compute
-// unit); volumes narrower than a quad keep the line scans in both phases.
+// Sweep work-groups of the volumes that take them, in their launch's order.
 void batch_sweep_items(BatchVol* vols, int count) {
     int32_t first[2] = {0, 0};
     for (int k = 0; k < count; ++k) {
         BatchVol& d = vols[k];
-        const int per = kWave / d.row_lanes, cls = d.By > 104 ? 0 : 1;
+        const int per = kWave / d.row_lanes, cls = batch_sweep_class(d.By);
         d.sweep_first[0] = first[0];
         d.sweep_first[1] = first[1];
-        if (d.Bx < 4) continue;
+        if (!batch_volume_sweeps({d.n, d.Bx, d.By, d.Bz})) continue;
         d.sweep_items[cls] = (d.n + per - 1) / per * batch_sweep_parts(d.Bz);
         first[cls] += d.sweep_items[cls];
         d.items[1] = d.items[2] = 0;
