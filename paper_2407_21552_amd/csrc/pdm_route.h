@@ -52,8 +52,10 @@ inline int sweep_waves(int np, int By) {
 // Microseconds the line scans take per megabyte of maps, one pass over lines
 // of m bricks (fits of measured passes: 0.67 at 96 bricks, 0.74 at 128, 0.91
 // at 199, 1.04 at 256: the longer the line, the larger its table and the fewer
-// the waves of a compute unit).
-inline double scan_us_per_mb(int m) { return 0.45 + 0.0023 * m; }
+// the waves of a compute unit).  Over 256 bricks another kernel takes the pass
+// (k_dist_global), whose tables do not grow with the line: 2.1 to 2.6 measured
+// from 257 to 8000 bricks.
+inline double scan_us_per_mb(int m) { return m > 256 ? 2.3 : 0.45 + 0.0023 * m; }
 
 // Whether the sweeps take all maps of a grid, and not the slices (0.36 us per
 // megabyte) and the z scans.  They run one work-group per group of 64/W maps
@@ -61,7 +63,8 @@ inline double scan_us_per_mb(int m) { return 0.45 + 0.0023 * m; }
 // so they win where there are many bytes for few steps: 64 maps of 256x256x199
 // bricks 901 us against 1217, 256 maps of 128x128x128 424 against 571; but 64
 // maps of 256x256x128 607 against 598, of 175x175x175 593 against 485, 256 of
-// 75x75x75 185 against 130.
+// 75x75x75 185 against 130.  Tall grids: 64 maps of 128x128x600 1143 against
+// 1848, of 64x64x3000 3895 against 2113, 32 of 128x128x1200 2000 against 1691.
 inline bool sweep_fits(int count, int Bx, int By, int Bz) {
     if (Bx < 4 || Bx > 256 || By > 256 || Bz < 2) return false;
     const int per = kWave / row_lanes(Bx);

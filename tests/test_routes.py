@@ -1,6 +1,21 @@
 """The cases that the GPU tests mean for the sweeps are on the sweeps' side of
 the rules, and reach every variant of the kernels."""
+import pytest
+
 import route_rules as R
+
+# (n, Bx, By, Bz), measured microseconds of the y and z passes by the sweeps and
+# by slices and z scans, where these differ by more than a fifth
+TALL = [((64, 64, 64, 3000), 3895, 2113), ((32, 64, 64, 8000), 10691, 2866), ((64, 128, 128, 300), 583, 887),
+        ((64, 128, 128, 600), 1143, 1848), ((64, 256, 256, 257), 1147, 2904), ((32, 256, 256, 400), 1514, 2454),
+        ((64, 256, 64, 500), 694, 1510), ((16, 256, 64, 2000), 2654, 1362), ((128, 100, 100, 700), 1417, 2698),
+        ((12, 256, 256, 300), 1073, 621), ((128, 16, 16, 4000), 3266, 555), ((255, 4, 4, 8000), 5801, 961)]
+
+
+@pytest.mark.parametrize("grid,sweeps,lines", TALL)
+def test_tall_grids_take_the_faster(grid, sweeps, lines):
+    assert R.sweep_fits(*grid) == (sweeps < lines)
+
 
 
 def test_single_cases_take_the_sweeps():
