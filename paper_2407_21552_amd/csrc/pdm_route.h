@@ -57,23 +57,36 @@ inline int sweep_waves(int np, int By) {
 // from 257 to 8000 bricks.
 inline double scan_us_per_mb(int m) { return m > 256 ? 2.3 : 0.45 + 0.0023 * m; }
 
+// Microseconds per step of a sweep over `groups` work-groups: 0.8 of issue, and
+// more the more work-groups' rows are in flight, above all where a wave's rows
+// are those of several maps, each in cache lines of its own.  Measured: W 64:
+// 0.80 (24 work-groups), 0.88 (64), 0.95 (128, no more at 256 and 510); W 32:
+// 0.83 (64), 1.11 (128), 1.15 to 1.36 (256); W 16: 1.15 (64), 1.1 to 1.56 (128).
+inline double sweep_step_us(int W, int64_t groups) {
+    if (W >= 64) return 0.8 + 0.0012 * (double)std::min<int64_t>(groups, 128);
+    return 0.8 + (W == 32 ? 0.0022 : 0.0055) * (double)std::min<int64_t>(groups, 256);
+}
+
 // Whether the sweeps take all maps of a grid, and not the slices (0.36 us per
 // megabyte) and the z scans.  They run one work-group per group of 64/W maps
-// and half of the planes, each a chain of steps of about 0.95 us at 16 waves,
-// so they win where there are many bytes for few steps: 64 maps of 256x256x199
-// bricks 901 us against 1217, 256 maps of 128x128x128 424 against 571; but 64
-// maps of 256x256x128 607 against 598, of 175x175x175 593 against 485, 256 of
-// 75x75x75 185 against 130.  Tall grids: 64 maps of 128x128x600 1143 against
-// 1848, of 64x64x3000 3895 against 2113, 32 of 128x128x1200 2000 against 1691.
+// and half of the planes, each a chain of steps, so they win where there are
+// many bytes for few steps: 64 maps of 256x256x199 bricks 901 us against 1217,
+// 256 maps of 128x128x128 424 against 571; but 64 maps of 256x256x128 607
+// against 598, of 175x175x175 593 against 485, 256 of 75x75x75 185 against 130.
+// Tall grids: 64 maps of 128x128x600 1143 against 1848, of 64x64x3000 3895
+// against 2113, 32 of 128x128x1200 2000 against 1691.  Narrow rows: 255 maps of
+// 60x128x200 786 against 609, 128 of 100x256x256 1342 against 1228; with 8 maps
+// to a wave (32 bricks and fewer) no size measured wins: 255 of 32x128x300 947
+// against 959, of 24x128x600 2616 against 1528.
 inline bool sweep_fits(int count, int Bx, int By, int Bz) {
-    if (Bx < 4 || Bx > 256 || By > 256 || Bz < 2) return false;
-    const int per = kWave / row_lanes(Bx);
+    if (Bx <= 32 || Bx > 256 || By > 256 || Bz < 2) return false;
+    const int W = row_lanes(Bx), per = kWave / W;
     const int64_t G = (int64_t)Bx * By * Bz;
     if (G * std::min(per, count) > INT32_MAX) return false;  // 32-bit offsets within a group
     const int np = (Bz + 1) / 2 + 1, nw = sweep_waves(np, By);
     const int64_t groups = 2 * (int64_t)((count + per - 1) / per);
     const double rounds = std::max(1.0, (double)groups / 256.0);
-    const double t_sweep = 2.0 * (0.95 * (double)sweep_steps(np, By, nw) * rounds + 8.0);
+    const double t_sweep = 2.0 * (sweep_step_us(W, groups) * (double)sweep_steps(np, By, nw) * rounds + 8.0);
     const double mb = 1e-6 * (double)G * count;
     return t_sweep < mb * (0.36 + scan_us_per_mb(Bz));
 }

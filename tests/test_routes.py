@@ -11,6 +11,18 @@ TALL = [((64, 64, 64, 3000), 3895, 2113), ((32, 64, 64, 8000), 10691, 2866), ((6
         ((64, 256, 64, 500), 694, 1510), ((16, 256, 64, 2000), 2654, 1362), ((128, 100, 100, 700), 1417, 2698),
         ((12, 256, 256, 300), 1073, 621), ((128, 16, 16, 4000), 3266, 555), ((255, 4, 4, 8000), 5801, 961)]
 
+# the same for rows of several maps to a wave, by more than a twelfth
+NARROW = [((255, 24, 128, 600), 2616, 1528), ((255, 31, 127, 300), 1259, 1022), ((255, 60, 128, 200), 786, 609),
+          ((255, 60, 160, 200), 945, 743), ((255, 64, 256, 256), 1646, 1479), ((255, 64, 128, 256), 898, 776),
+          ((255, 61, 127, 255), 979, 806), ((255, 64, 200, 128), 631, 462), ((128, 100, 256, 256), 1342, 1228),
+          ((255, 128, 256, 128), 856, 1080), ((255, 100, 128, 300), 956, 2913), ((255, 101, 129, 301), 1034, 3100),
+          ((256, 128, 128, 128), 424, 571), ((255, 160, 160, 128), 725, 885)]
+
+
+@pytest.mark.parametrize("grid,sweeps,lines", NARROW)
+def test_narrow_rows_take_the_faster(grid, sweeps, lines):
+    assert R.sweep_fits(*grid) == (sweeps < lines)
+
 
 @pytest.mark.parametrize("grid,sweeps,lines", TALL)
 def test_tall_grids_take_the_faster(grid, sweeps, lines):
