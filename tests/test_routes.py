@@ -16,7 +16,7 @@ NARROW = [((255, 24, 128, 600), 2616, 1528), ((255, 31, 127, 300), 1259, 1022), 
           ((255, 60, 160, 200), 945, 743), ((255, 64, 256, 256), 1646, 1479), ((255, 64, 128, 256), 898, 776),
           ((255, 61, 127, 255), 979, 806), ((255, 64, 200, 128), 631, 462), ((128, 100, 256, 256), 1342, 1228),
           ((255, 128, 256, 128), 856, 1080), ((255, 100, 128, 300), 956, 2913), ((255, 101, 129, 301), 1034, 3100),
-          ((256, 128, 128, 128), 424, 571), ((255, 160, 160, 128), 725, 885)]
+          ((256, 128, 128, 128), 424, 571), ((128, 130, 96, 256), 548, 595)]
 
 
 @pytest.mark.parametrize("grid,sweeps,lines", NARROW)
