@@ -517,18 +517,17 @@ pdm_status batch_prepare(const pdm_batch_volume* h_vols, int32_t count, const pd
                 order[b - 1] = t;
             }
     for (int32_t k = 0; k < count; ++k) vols[k] = tmp[order[k]];
-    // grouped launches: the y and z phases by sweeps, or the y phase by slices
+    // grouped launches: a volume's y and z phases by sweeps, or its y phase by slices
     if (c.single_launch == 0) {
         pdm::RouteGrid grids[PDM_BATCH_MAX];
         for (int32_t k = 0; k < count; ++k) grids[k] = {vols[k].n, vols[k].Bx, vols[k].By, vols[k].Bz};
-        if (pdm::batch_sweep_fits(grids, count))
-            pdm::batch_sweep_items(vols, count);
-        else
-            for (int32_t k = 0; k < count; ++k)
-                if (pdm::slice_y_fits(vols[k].Bx, vols[k].By)) {
-                    vols[k].slices = 1;
-                    vols[k].items[1] = 0;
-                }
+        if (pdm::batch_sweep_fits(grids, count)) pdm::batch_sweep_items(vols, count);
+        for (int32_t k = 0; k < count; ++k)
+            if (vols[k].sweep_items[0] + vols[k].sweep_items[1] == 0 &&
+                pdm::slice_y_fits(vols[k].Bx, vols[k].By)) {
+                vols[k].slices = 1;
+                vols[k].items[1] = 0;
+            }
     }
     totals[0] = totals[1] = totals[2] = 0;
     for (int ph = 0; ph < 3; ++ph)

@@ -98,25 +98,56 @@ inline int batch_sweep_parts(int Bz) { return Bz >= kSweepMinPlanes ? 2 : 1; }
 // rows: up to 104 rows (52 KB) three work-groups share a compute unit's LDS.
 inline int batch_sweep_class(int By) { return By > 104 ? 0 : 1; }
 
-// Whether a volume's y and z passes are sweeps in a batch that takes them.
-inline bool batch_volume_sweeps(const RouteGrid& g) { return g.Bx >= 4; }
+// Microseconds of slices and z scans for a volume of a batch, and of a brick row
+// of its sweeps (64/W maps at once).  The rows of a wave's maps lie in cache
+// lines of their own, so narrow rows cost more, and rows of at most 16 bricks
+// twice as much again where planes are no whole cache lines and neighbouring
+// waves share them.  Per thousand rows, from batches of one size by both
+// routes: 0.17 to 0.28 (W 4, whole lines), 0.36 to 0.6 (W 4, others), 0.2 to
+// 0.37 (W 8), about 2 (W 2) and 4.5 (W 1); 0.2 for the wider ones.
+inline double batch_lines_us(const RouteGrid& g) {
+    return 1e-6 * (double)g.Bx * g.By * g.Bz * g.n * (0.46 + 1.3 * scan_us_per_mb(g.Bz));
+}
+inline double batch_sweep_row_us(const RouteGrid& g) {
+    const int W = row_lanes(g.Bx);
+    if (W >= 16) return 0.2e-3;
+    if (W == 8) return 0.33e-3;
+    if (W == 4) return (g.Bx * g.By) % 128 == 0 ? 0.23e-3 : 0.45e-3;
+    return W == 2 ? 2e-3 : 4.5e-3;
+}
+inline double batch_sweep_rows(const RouteGrid& g) {
+    const int per = kWave / row_lanes(g.Bx);
+    return (double)((g.n + per - 1) / per) * g.By * g.Bz;
+}
 
-// Whether the sweeps take the y and z phases of a batch, and not the slices and
-// the z scans: their time follows all rows and the longest chain of steps, that
-// of the others the bytes (fits of the measured batches, sweeps against slices
-// and scans: 4 volumes of 900..1024 voxels per axis 2645 us against 3780, 12 of
-// 400..1000 2340 against 3230; 48 of 96..640 1833 against 1780, 6 of 300..640
-// 571 against 319, 48 of 60..200 194 against 92).
+// Whether a volume's y and z passes are sweeps in a batch that takes them: rows
+// of at most 32 bricks only where their sweeps cost less than their slices and
+// scans (2 volumes of 1024x1024x795 voxels with 12 of 20x1000x1000: 8715 us
+// with all swept, 4532 with none).
+inline bool batch_volume_sweeps(const RouteGrid& g) {
+    if (g.Bx < 4) return false;
+    return g.Bx > 32 || batch_sweep_row_us(g) * batch_sweep_rows(g) < batch_lines_us(g);
+}
+
+// Whether the sweeps take the y and z phases of a batch's volumes, as far as
+// batch_volume_sweeps lets them, and not the slices and the z scans: their time
+// follows all rows and the longest chain of steps, that of the others the bytes
+// (fits of the measured batches, sweeps against slices and scans: 4 volumes of
+// 900..1024 voxels per axis 2645 us against 3780, 12 of 400..1000 2340 against
+// 3230; 48 of 96..640 1833 against 1780, 6 of 300..640 571 against 319, 48 of
+// 60..200 194 against 92; whole builds of 24 of 64x1000x1000 4645 against 4252,
+// of 80x1000x1000 5923 against 5607, of 128x1000x1000 6120 against 7184).
 inline bool batch_sweep_fits(const RouteGrid* g, int count) {
     double rows = 0.0, t_lines = 0.0;
     int64_t chain = 0;
     for (int k = 0; k < count; ++k) {
-        const int per = kWave / row_lanes(g[k].Bx), parts = batch_sweep_parts(g[k].Bz);
-        rows += (double)((g[k].n + per - 1) / per) * g[k].By * g[k].Bz;
+        if (!batch_volume_sweeps(g[k])) continue;
+        const int parts = batch_sweep_parts(g[k].Bz);
+        rows += batch_sweep_row_us(g[k]) * batch_sweep_rows(g[k]);
         chain = std::max(chain, sweep_steps((g[k].Bz + parts - 1) / parts, g[k].By, kSweepBatchWaves));
-        t_lines += 1e-6 * (double)g[k].Bx * g[k].By * g[k].Bz * g[k].n * (0.46 + 1.3 * scan_us_per_mb(g[k].Bz));
+        t_lines += batch_lines_us(g[k]);
     }
-    return 0.2e-3 * rows + 0.84 * (double)chain + 30.0 < t_lines;
+    return rows + 0.8 * (double)chain + 30.0 < t_lines;
 }
 
 }  // namespace pdm

@@ -64,8 +64,9 @@ SWEEP_CASES = [((795, 1024, 1024), 64), ((500, 1013, 1010), 64), ((512, 512, 512
 
 # A batch of two large volumes and of small ones of every lane count, (nz, ny,
 # nx) and partitions: both classes of row counts, planes cut in two parts and
-# not, whole and ragged rows, map counts that fill a wave and that do not.
+# not, whole and ragged rows, map counts that fill a wave and that do not; among
+# them volumes of narrow rows that keep the scans.
 SWEEP_BATCH = [((800, 1000, 1010), 64), ((900, 1024, 1024), 61), ((36, 200, 400), 37), ((33, 197, 403), 37),
                ((60, 416, 256), 64), ((160, 80, 199), 33), ((7, 420, 217), 5), ((80, 8, 128), 64),
-               ((280, 387, 115), 19), ((64, 128, 64), 64), ((90, 70, 51), 7), ((100, 100, 27), 9),
+               ((600, 387, 123), 63), ((480, 380, 128), 64), ((64, 128, 64), 64), ((90, 70, 51), 7), ((100, 100, 27), 9),
                ((40, 50, 14), 64), ((61, 33, 9), 3)]

@@ -30,6 +30,45 @@ def test_tall_grids_take_the_faster(grid, sweeps, lines):
 
 
 
+# batches, (nx, ny, nz) voxels and how many with n partitions; measured
+# microseconds of the build with all volumes of at least 4 bricks a row swept and
+# with none, where these differ by more than a twentieth
+BATCHES = [([((56, 1000, 1000), 24)], 64, 5250, 4001), ([((64, 1000, 1000), 24)], 64, 4645, 4252),
+           ([((80, 1000, 1000), 24)], 64, 5924, 5607), ([((124, 1000, 1000), 24)], 64, 7655, 8155),
+           ([((128, 1000, 1000), 24)], 64, 6120, 7184), ([((64, 500, 500), 48)], 64, 2721, 1758),
+           ([((96, 500, 500), 48)], 64, 3006, 2534), ([((128, 500, 500), 48)], 64, 3126, 2851),
+           ([((64, 1000, 300), 48)], 64, 2968, 2018), ([((96, 1000, 300), 48)], 64, 3453, 2993),
+           ([((128, 1000, 300), 48)], 64, 3355, 3176), ([((64, 1024, 1024), 24)], 64, 2976, 3908),
+           ([((64, 640, 640), 48)], 64, 2521, 2680), ([((64, 1024, 1024), 48)], 64, 5842, 7821),
+           ([((128, 640, 640), 48)], 64, 3858, 4563), ([((128, 1024, 1024), 20)], 64, 5557, 5825),
+           ([((128, 512, 1024), 24)], 64, 2741, 3518), ([((128, 1024, 1024), 48)], 32, 6658, 7690),
+           ([((32, 1024, 1024), 24)], 64, 4465, 2280), ([((16, 1000, 1000), 24)], 64, 7646, 1492),
+           ([((48, 1000, 1000), 24)], 64, 4673, 3540), ([((68, 500, 500), 48)], 64, 2610, 2055),
+           ([((160, 1000, 1000), 24)], 64, 7596, 10150), ([((250, 640, 640), 24)], 64, 4534, 5076),
+           ([((132, 1000, 1000), 24)], 64, 7139, 8786), ([((300, 1024, 1024), 6)], 64, 4187, 4729),
+           ([((1024, 1024, 795), 1), ((12, 1000, 1000), 20)], 64, 2577, 3059),
+           ([((1024, 64, 1024), 24)], 64, 2918, 3498), ([((1024, 1024, 795), 2)], 64, 2054, 3227)]
+MIXED = [([((1024, 1024, 795), 2), ((32, 1000, 1000), 20)], 64), ([((1024, 1024, 795), 2), ((20, 1000, 1000), 12)], 64),
+         ([((1024, 1024, 795), 2), ((16, 1000, 1000), 4), ((30, 700, 900), 4), ((24, 1024, 1024), 4)], 64),
+         ([((1024, 1024, 795), 2), ((36, 1000, 1000), 16)], 64)]
+
+
+def _grids(sizes, n):
+    return [R.bricks(s[::-1], n) for s, count in sizes for _ in range(count)]
+
+
+@pytest.mark.parametrize("sizes,n,sweeps,lines", BATCHES)
+def test_batches_take_the_faster(sizes, n, sweeps, lines):
+    assert R.batch_fits(_grids(sizes, n)) == (sweeps < lines)
+
+
+@pytest.mark.parametrize("sizes,n", MIXED)
+def test_narrow_volumes_of_a_swept_batch_keep_the_scans(sizes, n):
+    grids = _grids(sizes, n)
+    assert R.batch_fits(grids)
+    assert [R.volume_sweeps(g) for g in grids] == [g[1] > 32 for g in grids]
+
+
 def test_single_cases_take_the_sweeps():
     seen = set()
     for shape, n in R.SWEEP_CASES:
@@ -49,7 +88,8 @@ def test_batch_takes_the_sweeps():
     assert R.batch_fits(grids)
     swept = [g for g in grids if R.volume_sweeps(g)]
     lanes = {R.lib().row_lanes(g[1]) for g in swept}
-    assert {8, 16, 32, 64} <= lanes
+    assert {4, 8, 16, 32, 64} <= lanes
+    assert any(g[1] >= 4 and not R.volume_sweeps(g) for g in grids)
     assert {R.lib().rows_class(g[2]) for g in swept} == {0, 1}
     assert any(R.lib().parts(g[3]) == 1 and g[2] > 1 for g in swept)
     for ragged in (False, True):  # several maps to a wave, the last wave not full
