@@ -356,6 +356,9 @@ __device__ __forceinline__ QuadMinMax<T> quad_ragged_rows(VP __restrict__ vol, i
 }
 
 // The quad's rows one at a time (a brick layer cut in z or y): few registers.
+// Cached loads: the last layer's waves run alone at the end, on a chain of
+// these, which non-temporal loads stretch (plain x pass of 1024x1024x795 134.5
+// -> 139 us).
 template <typename T, bool EDGE, typename VP>
 __device__ __forceinline__ QuadMinMax<T> quad_rows_looped(VP __restrict__ vol, int nx, int ny,
                                                           int z0, int y0, int zn, int yn, int x0) {
@@ -367,9 +370,10 @@ __device__ __forceinline__ QuadMinMax<T> quad_rows_looped(VP __restrict__ vol, i
             if (yy < yn) {
                 const int64_t off = ((int64_t)(z0 + zz) * ny + (y0 + yy)) * nx + xp;
                 if constexpr (sizeof(T) == 1)
-                    c.add(load16_nt(vol + off));
+                    c.add(__builtin_bit_cast(u32x4, load16(vol + off)));
                 else
-                    c.add(load16_nt(vol + off), load16_nt(vol + off + 8));
+                    c.add(__builtin_bit_cast(u32x4, load16(vol + off)),
+                          __builtin_bit_cast(u32x4, load16(vol + off + 8)));
             }
         }
     }
