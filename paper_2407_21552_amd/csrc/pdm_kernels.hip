@@ -359,11 +359,11 @@ __device__ __forceinline__ QuadMinMax<T> quad_ragged_rows(VP __restrict__ vol, i
 // Cached loads: the last layer's waves run alone at the end, on a chain of
 // these, which non-temporal loads stretch (plain x pass of 1024x1024x795 134.5
 // -> 139 us).
-template <typename T, bool EDGE, typename VP>
+template <typename T, bool EDGE, typename ACC = QuadColumns<T>, typename VP>
 __device__ __forceinline__ QuadMinMax<T> quad_rows_looped(VP __restrict__ vol, int nx, int ny,
                                                           int z0, int y0, int zn, int yn, int x0) {
     const int xp = EDGE ? min(x0, nx - 16) : x0;
-    QuadColumns<T> c;
+    ACC c;
     for (int zz = 0; zz < zn; ++zz) {
 #pragma unroll
         for (int yy = 0; yy < 4; ++yy) {
@@ -389,7 +389,7 @@ __device__ __forceinline__ QuadMinMax<T> quad_rows_looped(VP __restrict__ vol, i
 //   kFastWhole16  the same for 16-bit rows of a multiple of 16 voxels, brick by
 //             brick: the brick pass takes 82 registers instead of 98, a wave
 //             more per SIMD (1024x1024x400: 172 -> 163 us)
-//   kCompact  the same at the row end, but cut layers row by row: for a caller
+//   kCompact  as kFast at the row end, but cut layers row by row: for a caller
 //             whose register budget must stay that of the whole-quad path
 //             (with every unrolled path inlined, the compiler schedules the
 //             plain x pass for 190 registers instead of 97, which halves its
@@ -398,7 +398,13 @@ __device__ __forceinline__ QuadMinMax<T> quad_rows_looped(VP __restrict__ vol, i
 //             past the row end (with that path inlined as well, the plain x
 //             pass took 102 registers instead of 91 and 1% longer on the
 //             1024x1024x795 volume)
-enum QuadEdges { kFast, kFastWhole16, kCompact, kNoRowEnd };
+//   kNoRowEnd16  the same brick by brick, for 16-bit rows of at least 400
+//             voxels: with 25 or more of a wave's lanes on a quad the loads of 4
+//             waves fill the memory (1024x1024x400 144.8 -> 140.6 us, 448x448x600
+//             44.0 -> 43.5, 400x400x600 38.4 -> 38.3); on shorter rows the 5
+//             waves of the columns' 94 registers do better (320x320x900 34.5
+//             against 36.4, 160x160x2000 31.8 against 35.4)
+enum QuadEdges { kFast, kFastWhole16, kCompact, kNoRowEnd, kNoRowEnd16 };
 
 template <typename T, QuadEdges EDGES = kFast, typename VP>
 __device__ __forceinline__ QuadMinMax<T> quad_minmax(VP __restrict__ vol, int nx, int ny, int nz,
@@ -410,6 +416,11 @@ __device__ __forceinline__ QuadMinMax<T> quad_minmax(VP __restrict__ vol, int nx
         if (zn == 4 && yn == 4)
             return quad_whole_rows<T, false, false, QuadBricks16>(vol, nx, ny, z0, y0, zn, yn, x0);
         return quad_whole_rows<T, true, false, QuadBricks16>(vol, nx, ny, z0, y0, zn, yn, x0);
+    }
+    if constexpr (EDGES == kNoRowEnd16) {
+        if (zn == 4 && yn == 4)
+            return quad_whole_rows<T, false, false, QuadBricks16>(vol, nx, ny, z0, y0, zn, yn, x0);
+        return quad_rows_looped<T, false, QuadBricks16>(vol, nx, ny, z0, y0, zn, yn, x0);
     }
     constexpr bool kRowEnd = EDGES != kNoRowEnd;
     if (!kRowEnd || nx >= 16) {
@@ -2571,6 +2582,8 @@ hipError_t launch_plain_x(const PlainArgs& a, const AlphaBits& bits, hipStream_t
         PDM_LAUNCH_PLAIN(uint8_t, false, kNoRowEnd);
     else if (!a.runs && row_end)
         PDM_LAUNCH_PLAIN(uint16_t, false, kCompact);
+    else if (!a.runs && a.nx >= 400)
+        PDM_LAUNCH_PLAIN(uint16_t, false, kNoRowEnd16);
     else if (!a.runs)
         PDM_LAUNCH_PLAIN(uint16_t, false, kNoRowEnd);
     else

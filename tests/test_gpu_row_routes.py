@@ -1,5 +1,5 @@
 """The volume-reading passes at every width where their variant changes (under
-16 voxels, multiples of 16, rows that end inside a quad, on either side of 512
+16 voxels, multiples of 16, rows that end inside a quad, on either side of 400
 voxels), with brick layers cut in z and y and without, against the oracle."""
 import numpy as np
 import pytest
@@ -8,7 +8,7 @@ import oracle
 
 pytestmark = pytest.mark.gpu
 
-WIDTHS = [1, 3, 4, 15, 16, 17, 48, 63, 496, 500, 512, 516, 1040]
+WIDTHS = [1, 3, 4, 15, 16, 17, 48, 63, 384, 400, 403, 496, 500, 512, 516, 1040]
 TYPES = [(np.uint8, 256), (np.uint16, 4096), (np.uint16, 65536)]
 
 
