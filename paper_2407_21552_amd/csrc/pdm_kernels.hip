@@ -404,7 +404,10 @@ __device__ __forceinline__ QuadMinMax<T> quad_rows_looped(VP __restrict__ vol, i
 //             44.0 -> 43.5, 400x400x600 38.4 -> 38.3); on shorter rows the 5
 //             waves of the columns' 94 registers do better (320x320x900 34.5
 //             against 36.4, 160x160x2000 31.8 against 35.4)
-enum QuadEdges { kFast, kFastWhole16, kCompact, kNoRowEnd, kNoRowEnd16 };
+//   kNarrow   rows of fewer than 16 voxels (which the other compact ones do not
+//             read: with a path for them inlined, the row end's registers were
+//             102 and 114, and they took 15x400x400 u8 55 us, here 23)
+enum QuadEdges { kFast, kFastWhole16, kCompact, kNoRowEnd, kNoRowEnd16, kNarrow };
 
 template <typename T, QuadEdges EDGES = kFast, typename VP>
 __device__ __forceinline__ QuadMinMax<T> quad_minmax(VP __restrict__ vol, int nx, int ny, int nz,
@@ -422,19 +425,19 @@ __device__ __forceinline__ QuadMinMax<T> quad_minmax(VP __restrict__ vol, int nx
             return quad_whole_rows<T, false, false, QuadBricks16>(vol, nx, ny, z0, y0, zn, yn, x0);
         return quad_rows_looped<T, false, QuadBricks16>(vol, nx, ny, z0, y0, zn, yn, x0);
     }
-    constexpr bool kRowEnd = EDGES != kNoRowEnd;
-    if (!kRowEnd || nx >= 16) {
-        if (zn == 4 && yn == 4)
-            return quad_whole_rows<T, false, kRowEnd>(vol, nx, ny, z0, y0, zn, yn, x0);
-        if constexpr (EDGES == kFast)
-            return quad_whole_rows<T, true, kRowEnd>(vol, nx, ny, z0, y0, zn, yn, x0);
-        else
-            return quad_rows_looped<T, kRowEnd>(vol, nx, ny, z0, y0, zn, yn, x0);
+    if constexpr (EDGES != kNarrow) {
+        constexpr bool kRowEnd = EDGES != kNoRowEnd;
+        if (EDGES != kFast || nx >= 16) {
+            if (zn == 4 && yn == 4)
+                return quad_whole_rows<T, false, kRowEnd>(vol, nx, ny, z0, y0, zn, yn, x0);
+            if constexpr (EDGES == kFast)
+                return quad_whole_rows<T, true, kRowEnd>(vol, nx, ny, z0, y0, zn, yn, x0);
+            else
+                return quad_rows_looped<T, kRowEnd>(vol, nx, ny, z0, y0, zn, yn, x0);
+        }
     }
-    if constexpr (EDGES == kFast) {
-        if (nx >= 4) return quad_ragged_rows<T>(vol, nx, ny, z0, y0, zn, yn, x0);
-    }
-    // one voxel at a time (rows of fewer than 4 voxels; under 16 when not kFast)
+    if (nx >= 4) return quad_ragged_rows<T>(vol, nx, ny, z0, y0, zn, yn, x0);
+    // one voxel at a time (rows of fewer than 4 voxels)
     QuadMinMax<T> r;
 #pragma unroll
     for (int k = 0; k < 4; ++k) { r.mn[k] = 0xFFFFFFFFu; r.mx[k] = 0u; }
@@ -2575,19 +2578,28 @@ hipError_t launch_plain_x(const PlainArgs& a, const AlphaBits& bits, hipStream_t
 #define PDM_LAUNCH_PLAIN(T, RUNS, EDGES)                                                            \
     k_plain_x<T, RUNS, EDGES><<<nb, 256, 0, s>>>((const T*)a.vol, a.nx, a.ny, a.nz, a.Bx, a.By, rows, \
                                                  bits, a.nwords, a.levels, a.dist, a.store_vec)
-    const bool row_end = a.nx % 16 != 0;
-    if (a.bytes == 1 && row_end)
-        PDM_LAUNCH_PLAIN(uint8_t, false, kCompact);
-    else if (a.bytes == 1)
-        PDM_LAUNCH_PLAIN(uint8_t, false, kNoRowEnd);
-    else if (!a.runs && row_end)
+    const bool row_end = a.nx % 16 != 0, narrow = a.nx < 16;
+    if (a.bytes == 1) {
+        if (narrow)
+            PDM_LAUNCH_PLAIN(uint8_t, false, kNarrow);
+        else if (row_end)
+            PDM_LAUNCH_PLAIN(uint8_t, false, kCompact);
+        else
+            PDM_LAUNCH_PLAIN(uint8_t, false, kNoRowEnd);
+    } else if (a.runs) {
+        if (narrow)
+            PDM_LAUNCH_PLAIN(uint16_t, true, kNarrow);
+        else
+            PDM_LAUNCH_PLAIN(uint16_t, true, kCompact);
+    } else if (narrow) {
+        PDM_LAUNCH_PLAIN(uint16_t, false, kNarrow);
+    } else if (row_end) {
         PDM_LAUNCH_PLAIN(uint16_t, false, kCompact);
-    else if (!a.runs && a.nx >= 400)
+    } else if (a.nx >= 400) {
         PDM_LAUNCH_PLAIN(uint16_t, false, kNoRowEnd16);
-    else if (!a.runs)
+    } else {
         PDM_LAUNCH_PLAIN(uint16_t, false, kNoRowEnd);
-    else
-        PDM_LAUNCH_PLAIN(uint16_t, true, kCompact);
+    }
 #undef PDM_LAUNCH_PLAIN
     return hipGetLastError();
 }
