@@ -1024,16 +1024,21 @@ __global__ void __launch_bounds__(256) k_plain_cached_x(const T* __restrict__ bm
 
 // Calls f(k, value) for the voxels of the 4 bricks x = 4q..4q+3 of brick row
 // (bz, by) that lie inside the volume (k = brick within the quad), each at
-// least once; values of bricks outside the grid are unspecified.  Rows past
-// the volume's end in z or y repeat its last row, and a quad that runs past the
-// row end takes the row's last 16 voxels moved up to its own, the row's last
-// voxel after them: the same loads for every lane of the wave.  ROW_END: rows
-// may be no multiple of 16 voxels.  AHEAD: the next slice's rows are loaded
-// while one is looked up, for twice the registers: the EXACT POM pass, few
-// waves with much work each (509x487x451 u16: 108 -> 58 us with the row end
-// above), but not the plain pass, which streams (512x512x460 u16: 77 against
-// 88 us).
-template <typename T, bool ROW_END, bool AHEAD, typename F>
+// least once; values of bricks outside the grid are unspecified.  ROWS: how.
+//   kQuads    quads inside the row row by row, others voxel by voxel: fewest
+//             registers, for rows of a multiple of 16 voxels or of fewer than 16
+//   kRowEnd   rows past the volume's end in z or y repeat its last row, and a
+//             quad that runs past the row end takes the row's last 16 voxels
+//             moved up to its own, the row's last voxel after them: the same
+//             loads for every lane of the wave.  Rows of at least 16 voxels.
+//   kAnyAhead as kRowEnd, or voxel by voxel on shorter rows, and the next
+//             slice's rows are loaded while one is looked up, for twice the
+//             registers: the EXACT POM pass, few waves with much work each
+//             (509x487x451 u16: 108 -> 58 us with the row end above), but not
+//             the plain pass, which streams (512x512x460 u16: 77 against 88 us)
+enum VoxelRows { kQuads, kRowEnd, kAnyAhead };
+
+template <typename T, VoxelRows ROWS, typename F>
 __device__ __forceinline__ void quad_voxels(const T* __restrict__ vol, int nx, int ny, int nz, int q,
                                             int by, int bz, F f) {
     const int x0 = 16 * q;
@@ -1063,7 +1068,7 @@ __device__ __forceinline__ void quad_voxels(const T* __restrict__ vol, int nx, i
             t[4 * i + 3] = a.w;
         }
     };
-    if constexpr (!ROW_END) {  // row by row: fewest registers
+    if (ROWS == kQuads && x0 + 16 <= nx) {
         for (int zz = 0; zz < zn; ++zz) {
 #pragma unroll
             for (int yy = 0; yy < 4; ++yy) {
@@ -1074,7 +1079,7 @@ __device__ __forceinline__ void quad_voxels(const T* __restrict__ vol, int nx, i
                 }
             }
         }
-    } else if (nx >= 16) {
+    } else if (ROWS == kRowEnd || (ROWS == kAnyAhead && nx >= 16)) {
         const int xp = min(x0, nx - 16);
         uint32_t w[4][kWords], next[4][kWords];
         auto load_slice = [&](int zz, uint32_t (&t)[4][kWords]) {
@@ -1082,6 +1087,7 @@ __device__ __forceinline__ void quad_voxels(const T* __restrict__ vol, int nx, i
             for (int yy = 0; yy < 4; ++yy)
                 load(((int64_t)(z0 + min(zz, zn - 1)) * ny + (y0 + min(yy, yn - 1))) * nx + xp, t[yy]);
         };
+        constexpr bool AHEAD = ROWS == kAnyAhead;
         if (AHEAD) load_slice(0, w);
 #pragma unroll 1
         for (int zz = 0; zz < 4; ++zz) {
@@ -1155,7 +1161,7 @@ __global__ void __launch_bounds__(256) k_pom_exact_x(const T* __restrict__ vol, 
         for (int w = 0; w < NW; ++w) mk[k][w] = 0u;
     const uint32_t top = (uint32_t)levels - 1u;  // voxels >= levels break the precondition
     if (row_ok && 4 * q < Bx) {
-        quad_voxels<T, true, true>(vol, nx, ny, nz, q, by, bz, [&](int k, uint32_t val) {
+        quad_voxels<T, kAnyAhead>(vol, nx, ny, nz, q, by, bz, [&](int k, uint32_t val) {
             const uint32_t pid = s_part[umin(val, top)];
             const uint32_t bit = 1u << (pid & 31u);
 #pragma unroll
@@ -1181,7 +1187,7 @@ __global__ void __launch_bounds__(256) k_pom_exact_x(const T* __restrict__ vol, 
 // k_plain_exact_x: the plain method's occupancy in the EXACT reading (some
 // voxel of the brick has alpha != 0, looked up in the LDS bitmap) and its x
 // distances; long rows in 256-brick segments as in k_plain_x.
-template <typename T, bool ROW_END>
+template <typename T, VoxelRows ROWS>
 __global__ void __launch_bounds__(256) k_plain_exact_x(const T* __restrict__ vol, int nx, int ny,
                                                        int nz, int Bx, int By, int64_t rows,
                                                        AlphaBits bits, int nwords, int levels,
@@ -1203,7 +1209,7 @@ __global__ void __launch_bounds__(256) k_plain_exact_x(const T* __restrict__ vol
         const int q = s * kWave + lane;
         uint32_t o = 0;
         if (4 * q < Bx) {
-            quad_voxels<T, ROW_END, false>(vol, nx, ny, nz, q, by, bz, [&](int k, uint32_t val) {
+            quad_voxels<T, ROWS>(vol, nx, ny, nz, q, by, bz, [&](int k, uint32_t val) {
                 const uint32_t v = umin(val, top);
                 o |= ((s_words[v >> 5] >> (v & 31u)) & 1u) << k;
             });
@@ -2657,17 +2663,20 @@ hipError_t launch_pom_exact_x(const PomExactArgs& a, const Bounds& b, hipStream_
 hipError_t launch_plain_exact_x(const PlainArgs& a, const AlphaBits& bits, hipStream_t s) {
     const int64_t rows = (int64_t)a.By * a.Bz;
     const unsigned nb = blocks_for(rows, 4);
-#define PDM_LAUNCH_PLAIN_EXACT(T, ROW_END)                                                           \
-    k_plain_exact_x<T, ROW_END><<<nb, 256, 0, s>>>((const T*)a.vol, a.nx, a.ny, a.nz, a.Bx, a.By, rows, \
-                                                   bits, a.nwords, a.levels, a.dist, a.store_vec)
-    if (a.bytes == 1 && a.nx % 16 != 0)
-        PDM_LAUNCH_PLAIN_EXACT(uint8_t, true);
+#define PDM_LAUNCH_PLAIN_EXACT(T, ROWS)                                                              \
+    k_plain_exact_x<T, ROWS><<<nb, 256, 0, s>>>((const T*)a.vol, a.nx, a.ny, a.nz, a.Bx, a.By, rows, \
+                                                bits, a.nwords, a.levels, a.dist, a.store_vec)
+    // rows of under 16 voxels are read voxel by voxel, where registers count:
+    // 15x400x400 u8 59 us, and 105 beside the row end's path
+    const bool row_end = a.nx >= 16 && a.nx % 16 != 0;
+    if (a.bytes == 1 && row_end)
+        PDM_LAUNCH_PLAIN_EXACT(uint8_t, kRowEnd);
     else if (a.bytes == 1)
-        PDM_LAUNCH_PLAIN_EXACT(uint8_t, false);
-    else if (a.nx % 16 != 0)
-        PDM_LAUNCH_PLAIN_EXACT(uint16_t, true);
+        PDM_LAUNCH_PLAIN_EXACT(uint8_t, kQuads);
+    else if (row_end)
+        PDM_LAUNCH_PLAIN_EXACT(uint16_t, kRowEnd);
     else
-        PDM_LAUNCH_PLAIN_EXACT(uint16_t, false);
+        PDM_LAUNCH_PLAIN_EXACT(uint16_t, kQuads);
 #undef PDM_LAUNCH_PLAIN_EXACT
     return hipGetLastError();
 }
