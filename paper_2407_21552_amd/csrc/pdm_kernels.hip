@@ -1031,12 +1031,12 @@ __global__ void __launch_bounds__(256) k_plain_cached_x(const T* __restrict__ bm
 //             quad that runs past the row end takes the row's last 16 voxels
 //             moved up to its own, the row's last voxel after them: the same
 //             loads for every lane of the wave.  Rows of at least 16 voxels.
-//   kAnyAhead as kRowEnd, or voxel by voxel on shorter rows, and the next
-//             slice's rows are loaded while one is looked up, for twice the
-//             registers: the EXACT POM pass, few waves with much work each
-//             (509x487x451 u16: 108 -> 58 us with the row end above), but not
-//             the plain pass, which streams (512x512x460 u16: 77 against 88 us)
-enum VoxelRows { kQuads, kRowEnd, kAnyAhead };
+//   kAny      as kRowEnd, or voxel by voxel on shorter rows
+//   kAnyAhead as kAny, and the next slice's rows are loaded while one is looked
+//             up, for 15 to 30 registers more (without its row end the 8-bit
+//             instantiation is scheduled for 116 registers, not 93, and takes 3
+//             to 10% longer on the whole rows it is for)
+enum VoxelRows { kQuads, kRowEnd, kAny, kAnyAhead };
 
 template <typename T, VoxelRows ROWS, typename F>
 __device__ __forceinline__ void quad_voxels(const T* __restrict__ vol, int nx, int ny, int nz, int q,
@@ -1079,7 +1079,7 @@ __device__ __forceinline__ void quad_voxels(const T* __restrict__ vol, int nx, i
                 }
             }
         }
-    } else if (ROWS == kRowEnd || (ROWS == kAnyAhead && nx >= 16)) {
+    } else if (ROWS == kRowEnd || (ROWS != kQuads && nx >= 16)) {
         const int xp = min(x0, nx - 16);
         uint32_t w[4][kWords], next[4][kWords];
         auto load_slice = [&](int zz, uint32_t (&t)[4][kWords]) {
@@ -1131,7 +1131,7 @@ __device__ __forceinline__ void quad_voxels(const T* __restrict__ vol, int nx, i
 // mask words per brick, from an LDS table intensity -> partition), then the
 // wave computes every partition's x distances from those masks.  Reads the
 // volume once and writes n*G bytes.  64/W rows to a wave, as in k_pom_x.
-template <typename T, int NW>
+template <typename T, int NW, VoxelRows ROWS>
 __global__ void __launch_bounds__(256) k_pom_exact_x(const T* __restrict__ vol, int nx, int ny,
                                                      int nz, int Bx, int By, int64_t rows,
                                                      Bounds bounds, int n, int levels,
@@ -1161,7 +1161,7 @@ __global__ void __launch_bounds__(256) k_pom_exact_x(const T* __restrict__ vol, 
         for (int w = 0; w < NW; ++w) mk[k][w] = 0u;
     const uint32_t top = (uint32_t)levels - 1u;  // voxels >= levels break the precondition
     if (row_ok && 4 * q < Bx) {
-        quad_voxels<T, kAnyAhead>(vol, nx, ny, nz, q, by, bz, [&](int k, uint32_t val) {
+        quad_voxels<T, ROWS>(vol, nx, ny, nz, q, by, bz, [&](int k, uint32_t val) {
             const uint32_t pid = s_part[umin(val, top)];
             const uint32_t bit = 1u << (pid & 31u);
 #pragma unroll
@@ -2634,7 +2634,7 @@ hipError_t launch_plain_cached_x(const CachedArgs& a, const AlphaBits& bits, hip
     return hipGetLastError();
 }
 
-template <typename T>
+template <typename T, VoxelRows ROWS>
 static hipError_t launch_pom_exact_t(const PomExactArgs& a, const Bounds& b, hipStream_t s) {
     const int64_t rows = (int64_t)a.By * a.Bz;
     int W = 1;  // lanes per row: the power of two with 4W >= Bx, at most a wave
@@ -2642,8 +2642,8 @@ static hipError_t launch_pom_exact_t(const PomExactArgs& a, const Bounds& b, hip
     const unsigned nb = blocks_for(rows, 4 * (kWave / W));
     const int nw = (a.n + 31) / 32;
 #define PDM_LAUNCH_EXACT(NW)                                                                     \
-    k_pom_exact_x<T, NW><<<nb, 256, 0, s>>>((const T*)a.vol, a.nx, a.ny, a.nz, a.Bx, a.By, rows, b, \
-                                            a.n, a.levels, a.pdms, a.G, W)
+    k_pom_exact_x<T, NW, ROWS><<<nb, 256, 0, s>>>((const T*)a.vol, a.nx, a.ny, a.nz, a.Bx, a.By, \
+                                                  rows, b, a.n, a.levels, a.pdms, a.G, W)
     if (nw == 1)
         PDM_LAUNCH_EXACT(1);
     else if (nw == 2)
@@ -2656,8 +2656,20 @@ static hipError_t launch_pom_exact_t(const PomExactArgs& a, const Bounds& b, hip
     return hipGetLastError();
 }
 
+// The look-ahead takes a wave or two of a SIMD's 4 to 6 and pays where a wave's rows fill
+// its lanes and end on a quad: 1024x600x400 u8 at 32 partitions 86.8 -> 81.9 us,
+// 1008x600x400 u16 at 128 264 -> 251, 896x600x400 u8 69.7 -> 67.1.  On rows that
+// do not, fewer registers win: 1021x900x300 u16 at 64 178.7 with it, 174.1
+// without, 509x487x451 u16 at 32 55.1 and 51.4, 512x512x460 u16 56.5 and 52.7,
+// 528x528x500 u16 81.7 and 77.6; 640x640x500 is even (108 and 111 at 32
+// partitions, 146 and 143 at 64).  Above 128 partitions 8-bit volumes take 111
+// registers anyway and the look-ahead pays at every width (509x487x451 at 256
+// 165 -> 161, 528x528x500 327 -> 317).
 hipError_t launch_pom_exact_x(const PomExactArgs& a, const Bounds& b, hipStream_t s) {
-    return a.bytes == 1 ? launch_pom_exact_t<uint8_t>(a, b, s) : launch_pom_exact_t<uint16_t>(a, b, s);
+    const bool ahead = (a.nx >= 640 && a.nx % 16 == 0) || (a.bytes == 1 && a.n > 128);
+    if (a.bytes == 1)
+        return ahead ? launch_pom_exact_t<uint8_t, kAnyAhead>(a, b, s) : launch_pom_exact_t<uint8_t, kAny>(a, b, s);
+    return ahead ? launch_pom_exact_t<uint16_t, kAnyAhead>(a, b, s) : launch_pom_exact_t<uint16_t, kAny>(a, b, s);
 }
 
 hipError_t launch_plain_exact_x(const PlainArgs& a, const AlphaBits& bits, hipStream_t s) {

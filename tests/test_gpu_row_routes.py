@@ -37,3 +37,17 @@ def test_bricks_and_plain(nx, dtype, levels):
         e.full_recompute(alpha)
         assert np.array_equal(pdm.from_device(e.dist),
                               oracle.full_recompute(vol, alpha, levels, mode=oracle.EXACT))
+
+
+@pytest.mark.parametrize("dtype,levels,n", [(np.uint8, 256, 5), (np.uint16, 4096, 40), (np.uint16, 4096, 200)])
+@pytest.mark.parametrize("nx", [3, 15, 16, 31, 624, 640, 643, 1024])
+def test_exact_build(nx, dtype, levels, n):
+    import paper_2407_21552_amd as pdm
+    r = np.random.default_rng(nx + n)
+    vol = np.zeros((7, 10, nx), dtype)
+    at = r.integers(0, vol.size, max(2, vol.size // 100))
+    vol.reshape(-1)[at] = r.integers(0, levels, len(at))
+    bounds = np.array([(p * levels) // n for p in range(n + 1)], np.int32)
+    v = pdm.Volume(pdm.to_device(vol), levels, bounds, voxel_dtype=dtype, mode=pdm.EXACT)
+    v.build()
+    assert np.array_equal(pdm.from_device(v.pdms), oracle.pdms(vol, bounds, levels, mode=oracle.EXACT))
