@@ -1261,10 +1261,6 @@ constexpr int kScanLanes = 64;
 constexpr int kPitch = 68;      // entries per table row (>= kScanLanes)
 constexpr int kRows = 256;
 constexpr int kMaxLine = 256;   // longest line staged in LDS
-// Passes over at most this many lines use the LDS-staged kernel: they cannot
-// fill the chip's 1024 SIMDs with more than a few waves each, so per-wave
-// latency matters more than occupancy.
-constexpr int64_t kStagedMaxLines = 4 * 1024 * kScanLanes;
 // Steps per chunk of the global-memory scans, which serve lines of more than
 // 256 bricks and passes whose offsets exceed the register kernels' 31 bits
 // (values loaded into registers before their steps run).  Measured over all
@@ -2810,7 +2806,7 @@ hipError_t launch_distance_yz(uint8_t* maps, int count, int Bx, int By, int Bz, 
     for (int axis = 1; axis <= 2; ++axis) {
         const int m = axis == 1 ? By : Bz;
         if (m == 1) continue;  // a line of one brick is unchanged
-        if (axis == 1 && x_distances && slice_y_fits(Bx, By)) {
+        if (axis == 1 && x_distances && slice_y_wins(count, Bx, By, Bz)) {
             const hipError_t e = launch_slice_y(maps, count, Bx, By, Bz, s);
             if (e != hipSuccess) return e;
             continue;

@@ -29,10 +29,36 @@ inline int row_lanes(int Bx) {
     return W;
 }
 
-// Whether k_slice_y takes the y pass of these grids: whole quads of bricks in a
-// wave, rows in registers.  It is the faster one at every size measured, from
-// one map of 16x16x16 bricks (where both are a launch) up.
+// Whether k_slice_y can take the y pass of these grids: whole quads of bricks in
+// a wave, rows in registers.
 inline bool slice_y_fits(int Bx, int By) { return Bx >= 4 && Bx <= 256 && By >= 2 && By <= 256; }
+
+// Scans over at most this many lines run two lanes per line or stage them in
+// LDS: they cannot fill the chip's 1024 SIMDs with more than a few waves each,
+// so per-wave latency matters more than occupancy.
+constexpr int64_t kStagedMaxLines = 1 << 18;
+
+// Whether it takes the y pass of `count` maps, and not the line scans.  It is
+// the faster one for few lines (one map of 256x256x199 13 us against 24) and on
+// most grids (64 MB of maps: 128x128 planes 24 us against 57, 33x32 36 against
+// 51).  Not, with many lines, on
+//  - planes of at most 16 rows that leave two fifths of a row's lanes without a
+//    brick: the waves work on 32 rows and 4W bricks whatever the plane has
+//    (33x4 112 us against 93, 17x2 55 against 44, 132x8 1.13 times; but 48x4
+//    110 against 130, 200x16 0.75 times, 33x20 0.67 times);
+//  - planes of whole 64-byte blocks with rows of 4, 8 or 12 bricks: 16 to 64
+//    slices to a wave, each of its accesses in a cache line of its own at one
+//    alignment (8x16 47 us against 30, 12x64 65 against 49, 4x16 33 against 26;
+//    but 8x20 0.76 times, 5x16 31 against 32, 16x16 36 against 52); the scans'
+//    tables grow with the line, so 8 and 12 bricks up to 192 rows (250 MB:
+//    12x192 243 against 228, 8x256 233 against 251, 4x256 363 against 341).
+inline bool slice_y_wins(int count, int Bx, int By, int Bz) {
+    if (!slice_y_fits(Bx, By)) return false;
+    if ((int64_t)count * Bx * Bz <= kStagedMaxLines) return true;
+    const int W = row_lanes(Bx);
+    if (W >= 8 && By <= 16 && 5 * Bx <= 12 * W) return false;
+    return !(Bx % 4 == 0 && Bx <= 12 && (Bx * By) % 64 == 0 && (Bx == 4 || By <= 192));
+}
 
 // Steps of one sweep over np planes of By rows with NW waves.
 inline int64_t sweep_steps(int np, int By, int NW) {

@@ -12,6 +12,7 @@ SHIM = """
 #include "pdm_route.h"
 extern "C" {
 int sweep_fits(int n, int bx, int by, int bz) { return pdm::sweep_fits(n, bx, by, bz); }
+int slice_y_wins(int n, int bx, int by, int bz) { return pdm::slice_y_wins(n, bx, by, bz); }
 int row_lanes(int bx) { return pdm::row_lanes(bx); }
 int batch_fits(const int* g, int count) { return pdm::batch_sweep_fits((const pdm::RouteGrid*)g, count); }
 int volume_sweeps(const int* g) { return pdm::batch_volume_sweeps(*(const pdm::RouteGrid*)g); }
@@ -33,6 +34,10 @@ def lib():
 
 def sweep_fits(n, bx, by, bz):
     return bool(lib().sweep_fits(n, bx, by, bz))
+
+
+def slice_y_wins(n, bx, by, bz):
+    return bool(lib().slice_y_wins(n, bx, by, bz))
 
 
 def _ints(grids):

@@ -69,6 +69,24 @@ def test_narrow_volumes_of_a_swept_batch_keep_the_scans(sizes, n):
     assert [R.volume_sweeps(g) for g in grids] == [g[1] > 32 for g in grids]
 
 
+# (n, Bx, By, Bz), measured microseconds of the y pass by slices and by line
+# scans, where these differ by more than a twentieth
+Y_PASS = [((64, 8, 16, 4000), 46.6, 30.3), ((64, 8, 64, 1953), 61.6, 57.7), ((64, 4, 16, 4000), 33.0, 26.3),
+          ((64, 12, 64, 1302), 65.1, 48.9), ((64, 12, 32, 2604), 64.0, 48.9), ((64, 8, 32, 3906), 61.1, 51.7),
+          ((64, 33, 2, 4000), 103.8, 81.5), ((64, 33, 16, 1893), 61.0, 54.6), ((64, 17, 4, 4000), 58.0, 51.3),
+          ((64, 4, 17, 4000), 28.6, 47.5), ((64, 5, 64, 3125), 103.6, 134.2), ((64, 8, 100, 1250), 58.2, 65.7),
+          ((64, 16, 16, 3906), 35.5, 52.0), ((64, 17, 32, 1838), 42.2, 60.9), ((64, 33, 17, 1782), 58.0, 82.2),
+          ((64, 48, 4, 4000), 109.7, 129.7), ((64, 64, 2, 4000), 102.2, 139.0), ((64, 128, 128, 61), 23.6, 57.4),
+          ((64, 100, 8, 1250), 74.8, 93.0), ((64, 8, 64, 244), 10.5, 16.5), ((64, 4, 32, 976), 15.4, 20.6),
+          ((128, 4, 256, 1907), 362.6, 341.4), ((128, 8, 256, 953), 233.1, 251.4), ((128, 12, 192, 847), 242.9, 228.4),
+          ((1, 128, 128, 64), 7.2, 10.0), ((1, 33, 8, 64), 3.0, 4.6)]
+
+
+@pytest.mark.parametrize("grid,slices,scans", Y_PASS)
+def test_y_pass_takes_the_faster(grid, slices, scans):
+    assert R.slice_y_wins(*grid) == (slices < scans)
+
+
 def test_single_cases_take_the_sweeps():
     seen = set()
     for shape, n in R.SWEEP_CASES:
