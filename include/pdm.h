@@ -242,8 +242,9 @@ pdm_status pdm_batch_tf_update_ranges(const pdm_batch_range_update* h_items, int
  * transform) for up to PDM_BATCH_MAX volumes of different sizes, dtypes and
  * partition counts.  Three phases, each covering every volume: bricks + POM
  * x distances per group of brick rows, then all y passes, then all z passes;
- * either as three grouped launches or (cfg->single_launch) as ONE cooperative
- * launch of resident work-groups with a grid barrier between the phases.
+ * either as grouped launches, a few per phase, or (cfg->single_launch) as ONE
+ * cooperative launch of resident work-groups with a grid barrier between the
+ * phases.
  * Results are identical to the single-volume calls.  Every grid axis must be
  * <= 256 bricks (else PDM_E_UNSUPPORTED).  Voxel values are not range-checked
  * here (pdm_build_bricks reports them).
@@ -271,9 +272,11 @@ typedef struct {
     int32_t rows_per_item;  /* wave passes per first-phase work item, 1..256; 0 = 2 (a
                                pass covers 64/W brick rows, W = lanes per row, the
                                power of two >= Bx/4) */
-    int32_t lines_mult;     /* 64-line groups per y/z work item, 1..16; 0 = 1 */
+    int32_t lines_mult;     /* single launch: 64-line groups per y/z work item, 1..16;
+                               0 = 1.  The grouped launches take any value of the range
+                               and do not use it. */
     int32_t largest_first;  /* 1: order the volumes' items by decreasing work */
-    int32_t single_launch;  /* 0: three grouped launches; 1: one cooperative launch */
+    int32_t single_launch;  /* 0: grouped launches; 1: one cooperative launch */
 } pdm_batch_config;
 
 size_t pdm_batch_workspace_bytes(int32_t count);

@@ -629,7 +629,7 @@ def batch_build(items, workspace, config=None, stream=None) -> None:
     uint8 device tensor of batch_workspace_bytes(len(items)) bytes or more
     (it receives the descriptors; keep it until the stream has passed);
     config: None or dict(rows_per_item=, lines_mult=, largest_first=,
-    single_launch=)."""
+    single_launch=); lines_mult counts only with single_launch."""
     arr, keep = _batch_volumes(items)
     count = len(items)
     need = batch_workspace_bytes(count)

@@ -1,9 +1,10 @@
 """Autotuner for the batched build's launch shape.
 
 The batched build (pdm_batch_build) has four knobs that change its speed
-but not its result: three grouped launches or one cooperative launch, the
-brick rows per first-phase work item, the number of 64-line groups per y/z
-work item, and whether the largest volumes' items come first.
+but not its result: grouped launches or one cooperative launch, the brick
+rows per first-phase work item, whether the largest volumes' items come first
+and, for the cooperative launch only, the number of 64-line groups per y/z
+work item.
 `tune_batch_build` times every candidate on the actual batch (HIP events on
 the launch stream, median of a few runs, after one warm-up, checking the
 workspace error word) and caches the fastest configuration under a
@@ -20,7 +21,7 @@ import os
 from . import _lib
 
 CANDIDATES = [dict(single_launch=sl, rows_per_item=r, lines_mult=m, largest_first=lf)
-              for sl in (0, 1) for r in (1, 2, 4) for m in (1, 2, 4) for lf in (0, 1)]
+              for sl, mults in ((0, (1,)), (1, (1, 2, 4))) for r in (1, 2, 4) for m in mults for lf in (0, 1)]
 
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "pdm_autotune.json")
 

@@ -2218,13 +2218,16 @@ __global__ void __launch_bounds__(256) k_batch_combine_maps(BatchMapsArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Batched build: the one-time initialisation of many volumes in three
-// grouped launches, each covering every volume of the batch:
+// Batched build: the one-time initialisation of many volumes in grouped
+// launches, or in one cooperative launch (k_batch_single):
 //   rows  item (volume, z slice, group of brick rows): brick [min,max] of the
 //         rows, then every partition's POM row and x distances (bricks and
 //         POM x fused: the volume is read once);
-//   y     item (volume, z slice, chunk of 64*lines_mult lines (p, x));
-//   z     item (volume, y row, chunk of 64*lines_mult lines (p, x)).
+//   y     slices (k_batch_slice_y), or 64 lines (p, x) of a slice; an item of
+//         the single launch is 64*lines_mult such lines;
+//   z     64 lines (p, y, x) of a volume's maps, neighbours in memory (single
+//         launch: 64*lines_mult);
+//   y, z  sweeps (k_batch_sweep) of the volumes that take them.
 // Launch boundaries order the phases, so no work-group waits on another.
 // The items of a phase are numbered volume by volume in descriptor order
 // (first[ph] is the running prefix).  Work-groups are handed to the XCDs

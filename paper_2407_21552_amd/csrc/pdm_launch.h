@@ -179,9 +179,10 @@ hipError_t launch_batch_combine(BatchArgs& a, hipStream_t s);
 // One launch for the a.count requests of `a` (sets first_block).
 hipError_t launch_batch_maps(BatchMapsArgs& a, hipStream_t s);
 // Uploads `count` descriptors into d_vols and zeroes d_sync, then runs the
-// build over totals[ph] items per phase: three grouped launches, or with
-// `single` one cooperative launch with grid barriers between the phases; a
-// y/z item covers 64*lines_mult lines.
+// build: grouped launches (totals[0] items of the rows phase; of the y and z
+// phases the volumes' slices, lines or sweeps), or with `single` one cooperative
+// launch with grid barriers between the phases over totals[ph] items each, a
+// y/z item covering 64*lines_mult lines.
 hipError_t launch_batch_build(const BatchVol* h_vols, int count, BatchVol* d_vols,
                               BatchSync* d_sync, const int64_t totals[3], int lines_mult,
                               int single, hipStream_t s);
