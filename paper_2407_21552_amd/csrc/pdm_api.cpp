@@ -668,7 +668,6 @@ pdm_status pdm_pom_exact_distance_x(const pdm_volume* v, const void* d_volume,
     a.bytes = v->dtype;
     a.n = n;
     a.levels = v->levels;
-    a.store_vec = g.bx % 4 == 0 && aligned(d_pdms, 4);
     return from_hip(pdm::launch_pom_exact_x(a, b, stream));
 }
 

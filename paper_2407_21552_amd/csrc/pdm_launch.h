@@ -159,7 +159,6 @@ struct PomExactArgs {
     uint8_t* pdms;
     int64_t G;
     int nx, ny, nz, Bx, By, Bz, bytes, n, levels;
-    int store_vec;
 };
 
 // Raster sweeps over the maps of one grid (pdm_sweep.hip).
