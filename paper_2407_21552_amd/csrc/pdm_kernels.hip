@@ -54,6 +54,7 @@
 
 namespace pdm {
 
+constexpr int kWave = 64;
 constexpr int kSegBricks = 4 * kWave;  // bricks of one x segment handled by a wave
 constexpr int kNone = 1 << 20;         // "no occupied brick": farther than any cap
 

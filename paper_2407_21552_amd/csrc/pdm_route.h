@@ -8,7 +8,7 @@
 
 namespace pdm {
 
-constexpr int kWave = 64;
+constexpr int kRowLanes = 64;  // a wave
 // Rows per step of a wave (between two barriers).  8 measured within 3% for
 // 256-row planes and 7% slower for 96 (fewer blocks than the lag of 16 waves
 // needs).
@@ -106,7 +106,7 @@ inline double sweep_step_us(int W, int64_t groups) {
 // against 959, of 24x128x600 2616 against 1528.
 inline bool sweep_fits(int count, int Bx, int By, int Bz) {
     if (Bx <= 32 || Bx > 256 || By > 256 || Bz < 2) return false;
-    const int W = row_lanes(Bx), per = kWave / W;
+    const int W = row_lanes(Bx), per = kRowLanes / W;
     const int64_t G = (int64_t)Bx * By * Bz;
     if (G * std::min(per, count) > INT32_MAX) return false;  // 32-bit offsets within a group
     const int np = (Bz + 1) / 2 + 1, nw = sweep_waves(np, By);
@@ -142,7 +142,7 @@ inline double batch_sweep_row_us(const RouteGrid& g) {
     return W == 2 ? 2e-3 : 4.5e-3;
 }
 inline double batch_sweep_rows(const RouteGrid& g) {
-    const int per = kWave / row_lanes(g.Bx);
+    const int per = kRowLanes / row_lanes(g.Bx);
     return (double)((g.n + per - 1) / per) * g.By * g.Bz;
 }
 

@@ -45,6 +45,7 @@
 
 namespace pdm {
 
+constexpr int kWave = 64;
 constexpr int kBufferRaw = 0x00020000;     // raw buffer, 32-bit data format (gfx9 family)
 constexpr uint32_t kBeyond = 0x01FF01FFu;  // a neighbour outside the row: above every distance
 constexpr uint32_t kCap2 = 0x00FF00FFu;    // two capped distances
