@@ -70,7 +70,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBPS = 8000.0  # MI355X HBM3E
 KERNEL_SRC = os.path.join(ROOT, "paper_2407_21552_amd", "csrc", "pdm_kernels.hip")
-MORE_KERNEL_SRC = [os.path.join(ROOT, "paper_2407_21552_amd", "csrc", f) for f in ("pdm_sweep.hip", "pdm_packed.h")]
+MORE_KERNEL_SRC = [os.path.join(ROOT, "paper_2407_21552_amd", "csrc", f) for f in ("pdm_sweep.hip", "pdm_packed.h", "pdm_route.h")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_tube_tree_1024x1024x795.md")
 
 # paper's numbers (RTX 4090, OpenGL), kingsnake 1024x1024x795, 64 partitions
@@ -111,6 +111,52 @@ def load_traffic():
     if rec.get("kernel_source_sha256_16") != kernel_hash():
         return None
     return rec
+
+
+def tube_tree_step(pdm, v, t_vol, bounds, n, alphas, d_full, d_cached, stream, event):
+    """One timed step: the calls a program makes, whole.  Returns the events
+    around the build's calls and, per TF, around the update's and the two
+    recomputes'."""
+    desc = v.desc
+    e = [event()]
+    pdm.build_bricks(desc, t_vol, v.bmin, v.bmax, None, stream)
+    e.append(event())
+    pdm.build_partitions(desc, v.bmin, v.bmax, bounds, v.pdms, stream)
+    e.append(event())
+    tf = []
+    for a in alphas:
+        f = [event()]
+        pdm.tf_update(desc, v.pdms, bounds, a, v.dist, stream)
+        f.append(event())
+        pdm.full_recompute(desc, t_vol, a, d_full, stream)
+        f.append(event())
+        pdm.full_recompute_cached(desc, v.bmin, v.bmax, a, d_cached, stream)
+        f.append(event())
+        tf.append(f)
+    return e, tf
+
+
+def x_pass_leg(pdm, v, t_vol, bounds, alphas, stream, event):
+    """The x passes by themselves (outside the step, whose calls run them and
+    the y and z passes together): events around the plain method's over the
+    volume and over the cached ranges per TF, and around the build's."""
+    desc = v.desc
+    d = v.dist.clone()
+    pdms = v.pdms.clone()
+    tf, build = [], []
+    for a in alphas:
+        f = [event()]
+        pdm.plain_distance_x(desc, t_vol, a, d, stream)
+        f.append(event())
+        pdm.plain_cached_distance_x(desc, v.bmin, v.bmax, a, d, stream)
+        f.append(event())
+        tf.append(f)
+    for _ in range(5):
+        e = [event()]
+        pdm.pom_distance_x(desc, v.bmin, v.bmax, bounds, pdms, stream)
+        e.append(event())
+        build.append(e)
+    return tf, build
 
 
 def range_table_leg(pdm, torch, stream, v, desc, bounds, alphas, masks, n, G, max_level):
@@ -293,33 +339,17 @@ def main():
         return b
 
     stream = torch.cuda.current_stream()
-    ev = lambda: torch.cuda.Event(enable_timing=True)
     d_cached = torch.empty_like(v.dist)
 
+    def event():
+        e = torch.cuda.Event(enable_timing=True)
+        e.record(stream)
+        return e
+
     def run_step(rec):
-        e = [ev() for _ in range(4)]
-        e[0].record(stream)
-        pdm.build_bricks(desc, t_vol, v.bmin, v.bmax, None, stream)
-        e[1].record(stream)
-        pdm.pom_distance_x(desc, v.bmin, v.bmax, bounds, v.pdms, stream)
-        e[2].record(stream)
-        pdm.distance_yz(desc, v.pdms, n, stream)
-        e[3].record(stream)
+        e, tf = tube_tree_step(pdm, v, t_vol, bounds, n, alphas, d_full, d_cached, stream, event)
         rec["build"].append(e)
-        for a in alphas:
-            f = [ev() for _ in range(6)]
-            f[0].record(stream)
-            pdm.tf_update(desc, v.pdms, bounds, a, v.dist, stream)
-            f[1].record(stream)
-            pdm.plain_distance_x(desc, t_vol, a, d_full, stream)
-            f[2].record(stream)
-            pdm.distance_yz(desc, d_full, 1, stream)
-            f[3].record(stream)
-            pdm.plain_cached_distance_x(desc, v.bmin, v.bmax, a, d_cached, stream)
-            f[4].record(stream)
-            pdm.distance_yz(desc, d_cached, 1, stream)
-            f[5].record(stream)
-            rec["tf"].append(f)
+        rec["tf"].extend(tf)
 
     log(f"warmup {args.warmup} step(s) ...")
     for _ in range(args.warmup):
@@ -338,15 +368,10 @@ def main():
 
     el = lambda a, b: a.elapsed_time(b)
     bricks_ms = [el(e[0], e[1]) for e in rec["build"]]
-    pomx_ms = [el(e[1], e[2]) for e in rec["build"]]
-    dyz_n_ms = [el(e[2], e[3]) for e in rec["build"]]
+    parts_ms = [el(e[1], e[2]) for e in rec["build"]]
     upd_ms = [el(f[0], f[1]) for f in rec["tf"]]
-    plx_ms = [el(f[1], f[2]) for f in rec["tf"]]
-    dyz1_ms = [el(f[2], f[3]) for f in rec["tf"]]
-    cx_ms = [el(f[3], f[4]) for f in rec["tf"]]
-    cyz_ms = [el(f[4], f[5]) for f in rec["tf"]]
-    full_ms = [a + b for a, b in zip(plx_ms, dyz1_ms)]
-    cached_ms = [a + b for a, b in zip(cx_ms, cyz_ms)]
+    full_ms = [el(f[1], f[2]) for f in rec["tf"]]
+    cached_ms = [el(f[2], f[3]) for f in rec["tf"]]
     upd_bytes = [(k + 1) * G for k in s_sizes] * args.steps
     sb = step_bytes()
 
@@ -355,6 +380,15 @@ def main():
     # brick ranges
     assert bool((v.dist <= d_full).all().item()), "D' > D"
     assert torch.equal(d_full, d_cached), "cached-range D differs from D"
+
+    log("the x passes by themselves ...")
+    x_tf, x_build = x_pass_leg(pdm, v, t_vol, bounds, alphas, stream, event)
+    torch.cuda.synchronize()
+    plx_ms = [el(f[0], f[1]) for f in x_tf]
+    cx_ms = [el(f[1], f[2]) for f in x_tf]
+    pomx = float(np.median([el(e[0], e[1]) for e in x_build]))
+    full_mean, cached_mean = float(np.mean(full_ms)), float(np.mean(cached_ms))
+    cached_x_mean = float(np.mean(cx_ms))
 
     # the same TFs through the range table (outside the step: an option of
     # the update, not one of the method's steps)
@@ -390,10 +424,13 @@ def main():
                                                     / k["algorithmic_bytes_per_launch"], 4)
         return r
 
+    # the step's time by phase: the x passes' share from the leg above
+    calls = len(full_ms)
     total_by_kernel = {
-        "k_plain_x": sum(plx_ms), "y/z scans, one map (k_dist_pairs)": sum(dyz1_ms) + sum(cyz_ms),
-        "k_combine": sum(upd_ms), "k_plain_cached_x": sum(cx_ms), "k_bricks": sum(bricks_ms),
-        "k_pom_x": sum(pomx_ms), "y/z scans, all partitions (k_dist_lines)": sum(dyz_n_ms)}
+        "k_plain_x": plain_avg_ms * calls, "k_combine": sum(upd_ms), "k_plain_cached_x": cached_x_mean * calls,
+        "y and z passes, one map": (full_mean - plain_avg_ms + cached_mean - cached_x_mean) * calls,
+        "k_bricks": sum(bricks_ms), "k_pom_x": pomx * args.steps,
+        "y and z passes, all partitions": sum(parts_ms) - pomx * args.steps}
 
     def ms_stats(xs):
         return {"p50_ms": round(pct(xs, 50), 4), "p90_ms": round(pct(xs, 90), 4),
@@ -424,11 +461,11 @@ def main():
                       "mean_active_partitions": round(float(np.mean(s_sizes)), 2)},
         "full_recompute": {**ms_stats(full_ms),
                            "occupancy_x_mean_ms": round(plain_avg_ms, 4),
-                           "distance_yz_mean_ms": round(float(np.mean(dyz1_ms)), 4),
+                           "distance_yz_mean_ms": round(full_mean - plain_avg_ms, 4),
                            "GBps": round(T * plain_bytes * args.steps / (sum(full_ms) * 1e-3) / 1e9, 1)},
         "full_recompute_cached": {**ms_stats(cached_ms),
-                                  "occupancy_x_mean_ms": round(float(np.mean(cx_ms)), 4),
-                                  "distance_yz_mean_ms": round(float(np.mean(cyz_ms)), 4),
+                                  "occupancy_x_mean_ms": round(cached_x_mean, 4),
+                                  "distance_yz_mean_ms": round(cached_mean - cached_x_mean, 4),
                                   "bytes_per_call": cached_bytes,
                                   "GBps": round(T * cached_bytes * args.steps / (sum(cached_ms) * 1e-3) / 1e9, 1),
                                   "identical_to_full_recompute": True},
@@ -437,9 +474,9 @@ def main():
         "speedup_update_vs_cached": {"p50": round(pct(cached_ms, 50) / pct(upd_ms, 50), 2),
                                      "mean": round(float(np.mean(cached_ms)) / float(np.mean(upd_ms)), 2)},
         "build": {"bricks_ms": round(float(np.median(bricks_ms)), 4),
-                  "pom_x_ms": round(float(np.median(pomx_ms)), 4),
-                  "distance_yz_ms": round(float(np.median(dyz_n_ms)), 4),
-                  "total_ms": round(float(np.median(np.add(np.add(bricks_ms, pomx_ms), dyz_n_ms))), 4),
+                  "pom_x_ms": round(pomx, 4),
+                  "distance_yz_ms": round(float(np.median(parts_ms)) - pomx, 4),
+                  "total_ms": round(float(np.median(np.add(bricks_ms, parts_ms))), 4),
                   "bricks_GBps": round((V * s + 2 * G * s) / (np.median(bricks_ms) * 1e-3) / 1e9, 1)},
         "kernel_time_share": {k: round(t / sum(total_by_kernel.values()), 4)
                               for k, t in total_by_kernel.items()},
@@ -828,20 +865,23 @@ def run_configs(args):
         full_b = [V * s + G] * T
         # build, median of 5
         bt = []
+        pdms_t = torch.empty_like(v.pdms)
         for _ in range(6):
             e = [ev()]
             pdm.build_bricks(desc, t_vol, v.bmin, v.bmax, None, stream)
             e.append(ev())
-            pdm.pom_distance_x(desc, v.bmin, v.bmax, bounds, v.pdms, stream)
+            pdm.build_partitions(desc, v.bmin, v.bmax, bounds, v.pdms, stream)
             e.append(ev())
-            pdm.distance_yz(desc, v.pdms, n, stream)
+            # the x pass by itself (the call above runs it with y and z)
+            pdm.pom_distance_x(desc, v.bmin, v.bmax, bounds, pdms_t, stream)
             e.append(ev())
             bt.append(e)
         torch.cuda.synchronize()
         bt = bt[1:]
-        build = {k: round(float(np.median([e[i].elapsed_time(e[i + 1]) for e in bt])), 4)
-                 for i, k in enumerate(("bricks_ms", "pom_x_ms", "distance_yz_ms"))}
-        build["total_ms"] = round(sum(build.values()), 4)
+        bricks, parts, pomx = (float(np.median([e[i].elapsed_time(e[i + 1]) for e in bt])) for i in range(3))
+        build = {"bricks_ms": round(bricks, 4), "pom_x_ms": round(pomx, 4),
+                 "distance_yz_ms": round(parts - pomx, 4), "total_ms": round(bricks + parts, 4)}
+        del pdms_t
 
         def busy(cold, k):
             # the device must be busy when the start event is recorded, or the
@@ -865,18 +905,11 @@ def run_configs(args):
             return [x.elapsed_time(y) for x, y in out]
 
         def full_phases(cold, exact=False):
-            occ_x = pdm.plain_exact_distance_x if exact else pdm.plain_distance_x
-            out = []
-            for k, a in enumerate(alphas):
-                busy(cold, k)
-                e0 = ev()
-                occ_x(desc, t_vol, a, d_full, stream)
-                e1 = ev()
-                pdm.distance_yz(desc, d_full, 1, stream)
-                e2 = ev()
-                out.append((e0, e1, e2))
-            torch.cuda.synchronize()
-            return ([x.elapsed_time(y) for x, y, _ in out], [y.elapsed_time(z) for _, y, z in out])
+            """Milliseconds of the full recompute per TF, and of its x pass run by itself."""
+            x = pdm.plain_exact_distance_x if exact else pdm.plain_distance_x
+            full = pdm.full_recompute_exact if exact else pdm.full_recompute
+            return (timed(cold, lambda a: full(desc, t_vol, a, d_full, stream)),
+                    timed(cold, lambda a: x(desc, t_vol, a, d_full, stream)))
 
         upd = lambda a: pdm.tf_update(desc, v.pdms, bounds, a, v.dist, stream)
         cached = lambda a: pdm.full_recompute_cached(desc, v.bmin, v.bmax, a, d_full, stream)
@@ -887,13 +920,12 @@ def run_configs(args):
         for mode in ("warm", "cold"):
             log(f"{name}: {T} TFs, {mode} ...")
             u = timed(mode == "cold", upd)
-            ox, yz = full_phases(mode == "cold")
-            fm = [a + b for a, b in zip(ox, yz)]
+            fm, ox = full_phases(mode == "cold")
             cm = timed(mode == "cold", cached)
             rec[mode] = {"tf_update": stats(u, upd_b, small),
                          "full_recompute": {**stats(fm, full_b, small),
                                             "occupancy_x_mean_ms": round(float(np.mean(ox)), 4),
-                                            "distance_yz_mean_ms": round(float(np.mean(yz)), 4)},
+                                            "distance_yz_mean_ms": round(float(np.mean(fm)) - float(np.mean(ox)), 4)},
                          "full_recompute_cached": stats(cm, cached_b, True),
                          "speedup_p50": round(pct(fm, 50) / pct(u, 50), 2),
                          "speedup_vs_cached_p50": round(pct(cm, 50) / pct(u, 50), 2)}
@@ -910,26 +942,25 @@ def run_configs(args):
                 e = [ev()]
                 pdm.pom_exact_distance_x(desc, t_vol, bounds, pdms_x, stream)
                 e.append(ev())
-                pdm.distance_yz(desc, pdms_x, n, stream)
+                pdm.build_partitions_exact(desc, t_vol, bounds, pdms_x, stream)
                 e.append(ev())
                 bx.append(e)
             torch.cuda.synchronize()
             bx = bx[1:]
-            xb = {"pom_exact_x_ms": round(float(np.median([e[0].elapsed_time(e[1]) for e in bx])), 4),
-                  "distance_yz_ms": round(float(np.median([e[1].elapsed_time(e[2]) for e in bx])), 4)}
-            xb["total_ms"] = round(xb["pom_exact_x_ms"] + xb["distance_yz_ms"], 4)
+            pomx, total = (float(np.median([e[i].elapsed_time(e[i + 1]) for e in bx])) for i in range(2))
+            xb = {"pom_exact_x_ms": round(pomx, 4), "distance_yz_ms": round(total - pomx, 4),
+                  "total_ms": round(total, 4)}
             xupd = lambda a: pdm.tf_update(desc, pdms_x, bounds, a, d_xu, stream)
             timed(False, xupd)  # warm-up
             xrec = {}
             for mode in ("warm", "cold"):
                 log(f"{name}: EXACT, {T} TFs, {mode} ...")
                 u = timed(mode == "cold", xupd)
-                ox, yz = full_phases(mode == "cold", exact=True)
-                fm = [a + b for a, b in zip(ox, yz)]
+                fm, ox = full_phases(mode == "cold", exact=True)
                 xrec[mode] = {"tf_update": stats(u, upd_b, small),
                               "full_recompute": {**stats(fm, full_b, small),
                                                  "occupancy_x_mean_ms": round(float(np.mean(ox)), 4),
-                                                 "distance_yz_mean_ms": round(float(np.mean(yz)), 4)}}
+                                                 "distance_yz_mean_ms": round(float(np.mean(fm)) - float(np.mean(ox)), 4)}}
             # tightness on three TFs: D' and D in both readings
             cmp_ = []
             for a in alphas[:3]:
