@@ -1028,16 +1028,25 @@ __global__ void __launch_bounds__(256) k_plain_cached_x(const T* __restrict__ bm
 // least once; values of bricks outside the grid are unspecified.  ROWS: how.
 //   kQuads    quads inside the row row by row, others voxel by voxel: fewest
 //             registers, for rows of a multiple of 16 voxels or of fewer than 16
-//   kRowEnd   rows past the volume's end in z or y repeat its last row, and a
-//             quad that runs past the row end takes the row's last 16 voxels
-//             moved up to its own, the row's last voxel after them: the same
-//             loads for every lane of the wave.  Rows of at least 16 voxels.
+//   kRowEnd   rows past the volume's end in y repeat its last row, slices past
+//             its end in z are left out (496x151x2 u16, EXACT POM pass at 146
+//             partitions: 37.5 us with them, 29.3), and a quad that runs past
+//             the row end takes the row's last 16 voxels moved up to its own,
+//             the row's last voxel after them: the same loads for every lane of
+//             the wave.  Rows of at least 16 voxels.
 //   kAny      as kRowEnd, or voxel by voxel on shorter rows
 //   kAnyAhead as kAny, and the next slice's rows are loaded while one is looked
-//             up, for 15 to 30 registers more (without its row end the 8-bit
-//             instantiation is scheduled for 116 registers, not 93, and takes 3
-//             to 10% longer on the whole rows it is for)
-enum VoxelRows { kQuads, kRowEnd, kAny, kAnyAhead };
+//             up, for 15 to 30 registers more; slices past the volume's end in z
+//             repeat its last one (left out, it took 2% longer).  Without its
+//             row end the 8-bit instantiation is scheduled for 116 registers,
+//             not 93, and takes 3 to 10% longer on the whole rows it is for.
+//   kRowEndLean, kAnyLean  the same row after row, without those past the end in
+//             y: 50 to 75 registers, not 76 to 136, and the loads not all first.
+//             For volumes of fewer than 4 voxels in y, whose repeated rows
+//             would be looked up (640x2x5 u16, EXACT POM pass at 100 partitions:
+//             23.7 us with them, 19.1 without), and for the plain pass where
+//             there are waves enough (see its launch)
+enum VoxelRows { kQuads, kRowEnd, kAny, kAnyAhead, kRowEndLean, kAnyLean };
 
 template <typename T, VoxelRows ROWS, typename F>
 __device__ __forceinline__ void quad_voxels(const T* __restrict__ vol, int nx, int ny, int nz, int q,
@@ -1080,18 +1089,19 @@ __device__ __forceinline__ void quad_voxels(const T* __restrict__ vol, int nx, i
                 }
             }
         }
-    } else if (ROWS == kRowEnd || (ROWS != kQuads && nx >= 16)) {
+    } else if (ROWS == kRowEnd || ROWS == kRowEndLean || (ROWS != kQuads && nx >= 16)) {
         const int xp = min(x0, nx - 16);
+        constexpr bool AHEAD = ROWS == kAnyAhead, kLean = ROWS == kRowEndLean || ROWS == kAnyLean;
         uint32_t w[4][kWords], next[4][kWords];
         auto load_slice = [&](int zz, uint32_t (&t)[4][kWords]) {
 #pragma unroll
             for (int yy = 0; yy < 4; ++yy)
                 load(((int64_t)(z0 + min(zz, zn - 1)) * ny + (y0 + min(yy, yn - 1))) * nx + xp, t[yy]);
         };
-        constexpr bool AHEAD = ROWS == kAnyAhead;
+        const int slices = AHEAD ? 4 : zn;
         if (AHEAD) load_slice(0, w);
 #pragma unroll 1
-        for (int zz = 0; zz < 4; ++zz) {
+        for (int zz = 0; zz < slices; ++zz) {
             if (AHEAD) {
                 load_slice(min(zz + 1, 3), next);
                 __builtin_amdgcn_sched_barrier(0);  // the loads ahead of the lookups
@@ -1100,6 +1110,7 @@ __device__ __forceinline__ void quad_voxels(const T* __restrict__ vol, int nx, i
             }
 #pragma unroll
             for (int yy = 0; yy < 4; ++yy) {
+                if (kLean && yy >= yn) break;
                 if (xp != x0) {
                     const uint32_t last = w[yy][kWords - 1];
                     shift_voxels<(int)sizeof(T)>(w[yy], x0 - xp, sizeof(T) == 1 ? (last >> 24) * 0x01010101u
@@ -2664,12 +2675,18 @@ static hipError_t launch_pom_exact_t(const PomExactArgs& a, const Bounds& b, hip
 // 528x528x500 u16 81.7 and 77.6; 640x640x500 is even (108 and 111 at 32
 // partitions, 146 and 143 at 64).  Above 128 partitions 8-bit volumes take 111
 // registers anyway and the look-ahead pays at every width (509x487x451 at 256
-// 165 -> 161, 528x528x500 327 -> 317).
+// 165 -> 161, 528x528x500 327 -> 317).  Not on thin volumes, where most of its
+// slices would be repeated ones.
 hipError_t launch_pom_exact_x(const PomExactArgs& a, const Bounds& b, hipStream_t s) {
-    const bool ahead = (a.nx >= 640 && a.nx % 16 == 0) || (a.bytes == 1 && a.n > 128);
+    const bool thin = a.ny < 4;
+    const bool ahead = !thin && a.nz >= 16 && ((a.nx >= 640 && a.nx % 16 == 0) || (a.bytes == 1 && a.n > 128));
     if (a.bytes == 1)
-        return ahead ? launch_pom_exact_t<uint8_t, kAnyAhead>(a, b, s) : launch_pom_exact_t<uint8_t, kAny>(a, b, s);
-    return ahead ? launch_pom_exact_t<uint16_t, kAnyAhead>(a, b, s) : launch_pom_exact_t<uint16_t, kAny>(a, b, s);
+        return thin    ? launch_pom_exact_t<uint8_t, kAnyLean>(a, b, s)
+               : ahead ? launch_pom_exact_t<uint8_t, kAnyAhead>(a, b, s)
+                       : launch_pom_exact_t<uint8_t, kAny>(a, b, s);
+    return thin    ? launch_pom_exact_t<uint16_t, kAnyLean>(a, b, s)
+           : ahead ? launch_pom_exact_t<uint16_t, kAnyAhead>(a, b, s)
+                   : launch_pom_exact_t<uint16_t, kAny>(a, b, s);
 }
 
 hipError_t launch_plain_exact_x(const PlainArgs& a, const AlphaBits& bits, hipStream_t s) {
@@ -2681,14 +2698,26 @@ hipError_t launch_plain_exact_x(const PlainArgs& a, const AlphaBits& bits, hipSt
     // rows of under 16 voxels are read voxel by voxel, where registers count:
     // 15x400x400 u8 59 us, and 105 beside the row end's path
     const bool row_end = a.nx >= 16 && a.nx % 16 != 0;
-    if (a.bytes == 1 && row_end)
-        PDM_LAUNCH_PLAIN_EXACT(uint8_t, kRowEnd);
-    else if (a.bytes == 1)
-        PDM_LAUNCH_PLAIN_EXACT(uint8_t, kQuads);
-    else if (row_end)
-        PDM_LAUNCH_PLAIN_EXACT(uint16_t, kRowEnd);
-    else
-        PDM_LAUNCH_PLAIN_EXACT(uint16_t, kQuads);
+    // with 4 waves and more per SIMD (1024 of them) a wave more hides what the
+    // loads in flight hide below (100x100x100 u16 14.7 us, lean 17.6; 130x140x150
+    // 11.2 and 12.0; but 50x300x300 26.1 and 23.6, 509x487x451 53.8 and 46.7, u8
+    // 42.3 and 37.8)
+    const bool lean = a.ny < 4 || rows > 4096;
+    if (a.bytes == 1) {
+        if (row_end && lean)
+            PDM_LAUNCH_PLAIN_EXACT(uint8_t, kRowEndLean);
+        else if (row_end)
+            PDM_LAUNCH_PLAIN_EXACT(uint8_t, kRowEnd);
+        else
+            PDM_LAUNCH_PLAIN_EXACT(uint8_t, kQuads);
+    } else {
+        if (row_end && lean)
+            PDM_LAUNCH_PLAIN_EXACT(uint16_t, kRowEndLean);
+        else if (row_end)
+            PDM_LAUNCH_PLAIN_EXACT(uint16_t, kRowEnd);
+        else
+            PDM_LAUNCH_PLAIN_EXACT(uint16_t, kQuads);
+    }
 #undef PDM_LAUNCH_PLAIN_EXACT
     return hipGetLastError();
 }

@@ -17,7 +17,7 @@ TYPES = [(np.uint8, 256), (np.uint16, 4096), (np.uint16, 65536)]
 def test_bricks_and_plain(nx, dtype, levels):
     import paper_2407_21552_amd as pdm
     r = np.random.default_rng(nx + levels)
-    for nz, ny in ((8, 12), (7, 10), (5, 3)):
+    for nz, ny in ((8, 12), (7, 10), (5, 3), (2, 9), (6, 1)):
         # values near a border of the opacity's support, so that bricks differ
         vol = r.integers(levels // 4, levels // 2 + levels // 16, (nz, ny, nx)).astype(dtype)
         vol[r.random(vol.shape) < 0.02] = levels - 1
@@ -44,10 +44,11 @@ def test_bricks_and_plain(nx, dtype, levels):
 def test_exact_build(nx, dtype, levels, n):
     import paper_2407_21552_amd as pdm
     r = np.random.default_rng(nx + n)
-    vol = np.zeros((7, 10, nx), dtype)
-    at = r.integers(0, vol.size, max(2, vol.size // 100))
-    vol.reshape(-1)[at] = r.integers(0, levels, len(at))
     bounds = np.array([(p * levels) // n for p in range(n + 1)], np.int32)
-    v = pdm.Volume(pdm.to_device(vol), levels, bounds, voxel_dtype=dtype, mode=pdm.EXACT)
-    v.build()
-    assert np.array_equal(pdm.from_device(v.pdms), oracle.pdms(vol, bounds, levels, mode=oracle.EXACT))
+    for nz, ny in ((7, 10), (18, 7), (2, 9), (18, 3)):  # cut layers, with the look-ahead's slices and thin
+        vol = np.zeros((nz, ny, nx), dtype)
+        at = r.integers(0, vol.size, max(2, vol.size // 100))
+        vol.reshape(-1)[at] = r.integers(0, levels, len(at))
+        v = pdm.Volume(pdm.to_device(vol), levels, bounds, voxel_dtype=dtype, mode=pdm.EXACT)
+        v.build()
+        assert np.array_equal(pdm.from_device(v.pdms), oracle.pdms(vol, bounds, levels, mode=oracle.EXACT))
