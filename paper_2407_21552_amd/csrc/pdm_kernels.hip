@@ -405,10 +405,11 @@ __device__ __forceinline__ QuadMinMax<T> quad_rows_looped(VP __restrict__ vol, i
 //             44.0 -> 43.5, 400x400x600 38.4 -> 38.3); on shorter rows the 5
 //             waves of the columns' 94 registers do better (320x320x900 34.5
 //             against 36.4, 160x160x2000 31.8 against 35.4)
-//   kNarrow   rows of fewer than 16 voxels (which the other compact ones do not
-//             read: with a path for them inlined, the row end's registers were
-//             102 and 114, and they took 15x400x400 u8 55 us, here 23)
-enum QuadEdges { kFast, kFastWhole16, kCompact, kNoRowEnd, kNoRowEnd16, kNarrow };
+//   kNarrow   rows of 4 to 15 voxels (which the other compact ones do not read:
+//             with a path for them inlined, the row end's registers were 102 and
+//             114, and they took 15x400x400 u8 55 us, here 23)
+//   kTiny     rows of fewer than 4 voxels
+enum QuadEdges { kFast, kFastWhole16, kCompact, kNoRowEnd, kNoRowEnd16, kNarrow, kTiny };
 
 template <typename T, QuadEdges EDGES = kFast, typename VP>
 __device__ __forceinline__ QuadMinMax<T> quad_minmax(VP __restrict__ vol, int nx, int ny, int nz,
@@ -426,7 +427,7 @@ __device__ __forceinline__ QuadMinMax<T> quad_minmax(VP __restrict__ vol, int nx
             return quad_whole_rows<T, false, false, QuadBricks16>(vol, nx, ny, z0, y0, zn, yn, x0);
         return quad_rows_looped<T, false, QuadBricks16>(vol, nx, ny, z0, y0, zn, yn, x0);
     }
-    if constexpr (EDGES != kNarrow) {
+    if constexpr (EDGES != kNarrow && EDGES != kTiny) {
         constexpr bool kRowEnd = EDGES != kNoRowEnd;
         if (EDGES != kFast || nx >= 16) {
             if (zn == 4 && yn == 4)
@@ -437,7 +438,9 @@ __device__ __forceinline__ QuadMinMax<T> quad_minmax(VP __restrict__ vol, int nx
                 return quad_rows_looped<T, kRowEnd>(vol, nx, ny, z0, y0, zn, yn, x0);
         }
     }
-    if (nx >= 4) return quad_ragged_rows<T>(vol, nx, ny, z0, y0, zn, yn, x0);
+    // (its 16 rows, repeated past the end, take longer than the voxels of a layer
+    // of one or two slices: 5x300x2 recomputed in 16.4 us, 14.3 without)
+    if (EDGES != kTiny && nx >= 4 && (EDGES != kNarrow || zn > 2)) return quad_ragged_rows<T>(vol, nx, ny, z0, y0, zn, yn, x0);
     // one voxel at a time (rows of fewer than 4 voxels)
     QuadMinMax<T> r;
 #pragma unroll
@@ -2595,19 +2598,25 @@ hipError_t launch_plain_x(const PlainArgs& a, const AlphaBits& bits, hipStream_t
 #define PDM_LAUNCH_PLAIN(T, RUNS, EDGES)                                                            \
     k_plain_x<T, RUNS, EDGES><<<nb, 256, 0, s>>>((const T*)a.vol, a.nx, a.ny, a.nz, a.Bx, a.By, rows, \
                                                  bits, a.nwords, a.levels, a.dist, a.store_vec)
-    const bool row_end = a.nx % 16 != 0, narrow = a.nx < 16;
+    const bool row_end = a.nx % 16 != 0, narrow = a.nx < 16, tiny = a.nx < 4;
     if (a.bytes == 1) {
-        if (narrow)
+        if (tiny)
+            PDM_LAUNCH_PLAIN(uint8_t, false, kTiny);
+        else if (narrow)
             PDM_LAUNCH_PLAIN(uint8_t, false, kNarrow);
         else if (row_end)
             PDM_LAUNCH_PLAIN(uint8_t, false, kCompact);
         else
             PDM_LAUNCH_PLAIN(uint8_t, false, kNoRowEnd);
     } else if (a.runs) {
-        if (narrow)
+        if (tiny)
+            PDM_LAUNCH_PLAIN(uint16_t, true, kTiny);
+        else if (narrow)
             PDM_LAUNCH_PLAIN(uint16_t, true, kNarrow);
         else
             PDM_LAUNCH_PLAIN(uint16_t, true, kCompact);
+    } else if (tiny) {
+        PDM_LAUNCH_PLAIN(uint16_t, false, kTiny);
     } else if (narrow) {
         PDM_LAUNCH_PLAIN(uint16_t, false, kNarrow);
     } else if (row_end) {
