@@ -438,9 +438,9 @@ __device__ __forceinline__ QuadMinMax<T> quad_minmax(VP __restrict__ vol, int nx
                 return quad_rows_looped<T, kRowEnd>(vol, nx, ny, z0, y0, zn, yn, x0);
         }
     }
-    // (its 16 rows, repeated past the end, take longer than the voxels of a layer
-    // of one or two slices: 5x300x2 recomputed in 16.4 us, 14.3 without)
-    if (EDGES != kTiny && nx >= 4 && (EDGES != kNarrow || zn > 2)) return quad_ragged_rows<T>(vol, nx, ny, z0, y0, zn, yn, x0);
+    // (its 16 rows, repeated past the end, take longer than the voxels of a few
+    // rows: 5x300x2 recomputed in 16.4 us, 14.4 without, 6x1x908 25.3 and 22.6)
+    if (EDGES != kTiny && nx >= 4 && (EDGES != kNarrow || zn * yn > 8)) return quad_ragged_rows<T>(vol, nx, ny, z0, y0, zn, yn, x0);
     // one voxel at a time (rows of fewer than 4 voxels)
     QuadMinMax<T> r;
 #pragma unroll

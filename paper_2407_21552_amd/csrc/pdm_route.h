@@ -39,7 +39,9 @@ inline bool slice_y_fits(int Bx, int By) { return Bx >= 4 && Bx <= 256 && By >= 
 constexpr int64_t kStagedMaxLines = 1 << 18;
 
 // Whether it takes the y pass of `count` maps, and not the line scans.  It is
-// the faster one for few lines (one map of 256x256x199 13 us against 24) and on
+// the faster one for few lines (one map of 256x256x199 13 us against 24), but
+// for those of 2 or 3 bricks, which are a launch either way (one map of
+// 100x2x64 4.3 us against 3.6, 33x2x200 4.0 and 3.4; 8x2x64 3.2 and 3.4), and on
 // most grids (64 MB of maps: 128x128 planes 24 us against 57, 33x32 36 against
 // 51).  Not, with many lines, on
 //  - planes of at most 16 rows that leave two fifths of a row's lanes without a
@@ -54,7 +56,8 @@ constexpr int64_t kStagedMaxLines = 1 << 18;
 //    12x192 243 against 228, 8x256 233 against 251, 4x256 363 against 341).
 inline bool slice_y_wins(int count, int Bx, int By, int Bz) {
     if (!slice_y_fits(Bx, By)) return false;
-    if ((int64_t)count * Bx * Bz <= kStagedMaxLines) return true;
+    const int64_t lines = (int64_t)count * Bx * Bz;
+    if (lines <= kStagedMaxLines) return Bx <= 16 || By > 3 || lines > kStagedMaxLines / 2;
     const int W = row_lanes(Bx);
     if (W >= 8 && By <= 16 && 5 * Bx <= 12 * W) return false;
     return !(Bx % 4 == 0 && Bx <= 12 && (Bx * By) % 64 == 0 && (Bx == 4 || By <= 192));

@@ -79,7 +79,9 @@ Y_PASS = [((64, 8, 16, 4000), 46.6, 30.3), ((64, 8, 64, 1953), 61.6, 57.7), ((64
           ((64, 48, 4, 4000), 109.7, 129.7), ((64, 64, 2, 4000), 102.2, 139.0), ((64, 128, 128, 61), 23.6, 57.4),
           ((64, 100, 8, 1250), 74.8, 93.0), ((64, 8, 64, 244), 10.5, 16.5), ((64, 4, 32, 976), 15.4, 20.6),
           ((128, 4, 256, 1907), 362.6, 341.4), ((128, 8, 256, 953), 233.1, 251.4), ((128, 12, 192, 847), 242.9, 228.4),
-          ((1, 128, 128, 64), 7.2, 10.0), ((1, 33, 8, 64), 3.0, 4.6)]
+          ((1, 128, 128, 64), 7.2, 10.0), ((1, 33, 8, 64), 3.0, 4.6),
+          ((1, 100, 2, 64), 4.3, 3.6), ((3, 33, 2, 60), 4.2, 3.4), ((1, 17, 3, 64), 4.2, 3.9), ((1, 8, 2, 64), 3.2, 3.4),
+          ((6, 256, 2, 200), 5.6, 7.2)]
 
 
 @pytest.mark.parametrize("grid,slices,scans", Y_PASS)
