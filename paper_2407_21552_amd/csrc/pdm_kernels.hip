@@ -388,17 +388,18 @@ __device__ __forceinline__ QuadMinMax<T> quad_rows_looped(VP __restrict__ vol, i
 // layer cut in z or y, 16 voxels that run past the row end) are read.
 //   kFast     unrolled paths, every load before the first use
 //   kFastWhole16  the same for 16-bit rows of a multiple of 16 voxels, brick by
-//             brick: the brick pass takes 82 registers instead of 98, a wave
-//             more per SIMD (1024x1024x400: 172 -> 163 us)
+//             brick: the brick pass takes 82 registers, where the columns took
+//             98 when the two were measured, a wave less per SIMD
+//             (1024x1024x400: 172 -> 163 us; kFast has 85 since)
 //   kCompact  as kFast at the row end, but cut layers row by row: for a caller
 //             whose register budget must stay that of the whole-quad path
 //             (with every unrolled path inlined, the compiler schedules the
-//             plain x pass for 190 registers instead of 97, which halves its
+//             plain x pass for 190 registers instead of 96, which halves its
 //             occupancy on whole rows)
 //   kNoRowEnd as kCompact, for rows of a multiple of 16 voxels: no quad runs
 //             past the row end (with that path inlined as well, the plain x
 //             pass took 102 registers instead of 91 and 1% longer on the
-//             1024x1024x795 volume)
+//             1024x1024x795 volume; both have 94 to 96 since)
 //   kNoRowEnd16  the same brick by brick, for 16-bit rows of at least 400
 //             voxels: with 25 or more of a wave's lanes on a quad the loads of 4
 //             waves fill the memory (1024x1024x400 144.8 -> 140.6 us, 448x448x600
@@ -1039,12 +1040,12 @@ __global__ void __launch_bounds__(256) k_plain_cached_x(const T* __restrict__ bm
 //             the wave.  Rows of at least 16 voxels.
 //   kAny      as kRowEnd, or voxel by voxel on shorter rows
 //   kAnyAhead as kAny, and the next slice's rows are loaded while one is looked
-//             up, for 15 to 30 registers more; slices past the volume's end in z
+//             up, for 17 to 33 registers more; slices past the volume's end in z
 //             repeat its last one (left out, it took 2% longer).  Without its
 //             row end the 8-bit instantiation is scheduled for 116 registers,
 //             not 93, and takes 3 to 10% longer on the whole rows it is for.
 //   kRowEndLean, kAnyLean  the same row after row, without those past the end in
-//             y: 50 to 75 registers, not 76 to 136, and the loads not all first.
+//             y: 42 to 99 registers, not 76 to 146, and the loads not all first.
 //             For volumes of fewer than 4 voxels in y, whose repeated rows
 //             would be looked up (640x2x5 u16, EXACT POM pass at 100 partitions:
 //             23.7 us with them, 19.1 without), and for the plain pass where
@@ -2914,7 +2915,8 @@ hipError_t launch_batch_maps(BatchMapsArgs& a, hipStream_t s) {
 }
 
 // Line lengths of a batch's scan launches: a launch's tables are sized for its
-// longest line, so long lines would take the waves of short ones.
+// longest line, so long lines would take the waves of short ones.  By LDS, in
+// pieces of 1280 bytes, 32, 21, 14 and 9 one-wave work-groups fit a unit.
 constexpr int kScanClasses = 5;
 constexpr int kScanClass[kScanClasses] = {0, 64, 104, 160, kMaxLine};
 

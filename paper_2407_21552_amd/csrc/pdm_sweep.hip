@@ -32,9 +32,11 @@
 // and the final distance gives the same distances, since the final ones never
 // exceed one more than their neighbours' and the first sweep's are enough.
 //
-// Bound by instruction issue (about 40 instructions per row and wave in all;
-// a SIMD issues one per 4 cycles) and, where fewer work-groups than compute
-// units run, by their number.
+// Bound, where fewer work-groups than compute units run, by their number, and
+// on a unit by a mix: about 40 instructions per row and wave in all, of which
+// one issues per SIMD and 4 cycles.  64 maps of 256x256x199 (128 work-groups on
+// 256 units): a wave issues in 32% of its cycles, waits to issue in 33% and
+// waits for its barrier, ring or loads in 34%; 23% of the chip's vector slots.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
